@@ -27,6 +27,8 @@ template <class R, bool ASIAN, int SC>
 __global__ __launch_bounds__(BLOCK) void adjoint_forward_kernel(const PriceLaunch L)
 {
     __shared__ double red[BLOCK / 64][N_ACC];
+    if constexpr (sizeof(R) == 8)
+        load_fp64_tables<BLOCK>();
     const uint64_t np = L.n_paths;
     const uint64_t row = (uint64_t)blockIdx.x * BLOCK + threadIdx.x;
     const bool active = row < np;
@@ -68,6 +70,8 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(const PriceLaunch L, dou
                                                         double *__restrict__ per_path)
 {
     __shared__ double red[BLOCK / 64][N_ACC];
+    if constexpr (sizeof(R) == 8)
+        load_fp64_tables<BLOCK>();
     const uint64_t np = L.n_paths;
     const uint64_t row = (uint64_t)blockIdx.x * BLOCK + threadIdx.x;
     const bool active = row < np;

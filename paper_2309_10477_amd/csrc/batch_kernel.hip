@@ -92,6 +92,8 @@ void batch_kernel(const BatchOption *__restrict__ opts,
 {
     __shared__ uint32_t s_unit;
     __shared__ double red[BLOCK / 64][N_ACC];
+    if constexpr (sizeof(R) == 8)
+        load_fp64_tables<BLOCK>();
     R *my_scratch = reinterpret_cast<R *>(scratch + (uint64_t)blockIdx.x * scratch_per_block);
     const uint32_t n_units = (item_end - item_begin) * BATCH_UNITS;
     for (;;) {

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fp64_math.hpp"
 #include "inv_normal_coef.hpp"
 
 namespace heston {
@@ -85,6 +86,17 @@ __device__ __forceinline__ void box_muller(double ua, double ub, double &za, dou
     zb = rad * s;
 }
 
+// Box-Muller pair of two random words, in double: the map above at the words'
+// uniforms, through the LDS tables (load_fp64_tables).
+__device__ __forceinline__ void box_muller_words(uint32_t wa, uint32_t wb, double &za, double &zb)
+{
+    const double rad = sqrt_nonneg(neg2_log_uniform(wa));
+    double c, s;
+    cos_sin_uniform(wb, c, s);
+    za = rad * c;
+    zb = rad * s;
+}
+
 // Inverse standard normal CDF on the lower half.
 // Single precision, from 30-bit coordinates: xs in [0, 2^29) stands for
 // u = (xs + 1/2) 2^-30.  In the erfinv variable of Giles (2011), w =
@@ -135,14 +147,14 @@ __device__ __forceinline__ double inv_normal_lower(double u) { return normcdfinv
 
 // Real-typed helpers.
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double fast_sqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ double fast_sqrt(double x) { return sqrt_nonneg(x); }
 __device__ __forceinline__ float fast_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double fast_rsqrt(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double fast_rsqrt(double x) { return rsqrt_pos(x); }
 __device__ __forceinline__ float fast_exp(float x)
 {
     return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
 }
-__device__ __forceinline__ double fast_exp(double x) { return exp(x); }
+__device__ __forceinline__ double fast_exp(double x) { return exp_plain(x); }
 
 template <class R> __device__ __forceinline__ R to_real(double v) { return (R)v; }
 

@@ -42,6 +42,8 @@ __device__ __forceinline__ bool is_fixing(const uint32_t *fix_bits, uint32_t jf)
 }
 
 // Normals of steps (j, j+1) from one Philox block: counter (j >> 1, lo32 p, hi32 p, 0).
+// Double precision reads the LDS tables of fp64_math.hpp, which the kernel
+// loads first (load_fp64_tables).
 // LOG2_SCALED (single precision only): the normals come divided by
 // sqrt(2 ln 2) (box_muller_log2).
 template <class R, bool LOG2_SCALED = false>
@@ -56,8 +58,8 @@ __device__ __forceinline__ void philox_normals(uint32_t j, uint32_t plo, uint32_
         box_muller(uniform_f32(w.x), uniform_f32(w.y), za0, zb0);
         box_muller(uniform_f32(w.z), uniform_f32(w.w), za1, zb1);
     } else {
-        box_muller(uniform_f64(w.x), uniform_f64(w.y), za0, zb0);
-        box_muller(uniform_f64(w.z), uniform_f64(w.w), za1, zb1);
+        box_muller_words(w.x, w.y, za0, zb0);
+        box_muller_words(w.z, w.w, za1, zb1);
     }
 }
 
@@ -352,7 +354,7 @@ __device__ __forceinline__ void qe_draws(uint32_t j, uint32_t plo, uint32_t phi,
         box_muller(uniform_f32(w.x), uniform_f32(w.y), zs, zv);
         uv = uniform_f32(w.z);
     } else {
-        box_muller(uniform_f64(w.x), uniform_f64(w.y), zs, zv);
+        box_muller_words(w.x, w.y, zs, zv);
         uv = uniform_f64(w.z);
     }
 }

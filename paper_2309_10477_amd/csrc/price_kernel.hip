@@ -118,7 +118,7 @@ template <class R> __device__ __forceinline__ Grid<R> grid(const StepCoef &c, do
 __device__ __forceinline__ float clamp0(float w) { return __builtin_amdgcn_fmed3f(w, 0.0f, 3.0e38f); }
 __device__ __forceinline__ double clamp0(double w) { return w > 0.0 ? w : 0.0; }
 __device__ __forceinline__ float exp2r(float y) { return __builtin_amdgcn_exp2f(y); }
-__device__ __forceinline__ double exp2r(double y) { return exp2(y); }
+__device__ __forceinline__ double exp2r(double y) { return exp2_plain(y); }
 
 // One scaled step on grid g; z1l = Z1 / ln 2, a_g = kappa theta dt^2 +
 // sigma^2 dt^2 (Z2^2 - 1) / 4, s_g = sigma dt Z2.  y leaves out the
@@ -209,7 +209,7 @@ template <class R> __device__ __forceinline__ QEGrid<R> qe_grid(const StepCoef &
 __device__ __forceinline__ float fast_log(float x) { return __builtin_amdgcn_logf(x) * (float)LN2; }
 __device__ __forceinline__ double fast_log(double x) { return log(x); }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double fast_rcp(double x) { return 1.0 / x; }
+__device__ __forceinline__ double fast_rcp(double x) { return rcp_pos(x); }
 
 // One QE step of one scenario, in two parts; z1l = Zs / ln 2, zv the normal
 // of the quadratic branch, uv the uniform of the exponential branch.
@@ -300,6 +300,8 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 6 : 1))) void pr
     constexpr bool FT = SCH == 0;
     extern __shared__ unsigned char smem_raw[];
     __shared__ double red[BLOCK / 64][NA];
+    if constexpr (sizeof(R) == 8 && RNG == 0)
+        load_fp64_tables<BLOCK>();
 
     const uint32_t rep = L.rep0 + blockIdx.y;
     const uint64_t M = L.paths_per_rep;
@@ -440,7 +442,7 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 6 : 1))) void pr
                 box_muller(uniform_f32(q.x), uniform_f32(q.y), zs, zv);
                 uv = uniform_f32(q.z);
             } else {
-                box_muller(uniform_f64(q.x), uniform_f64(q.y), zs, zv);
+                box_muller_words(q.x, q.y, zs, zv);
                 uv = uniform_f64(q.z);
             }
             const R z1l = zs * log2e;
