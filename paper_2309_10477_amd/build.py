@@ -39,6 +39,8 @@ FLAGS = [
 ]
 PER_FILE = {
     "price_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    # the exact sampler waits on its own chains (four waves per SIMD): 2% faster
+    "exact_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }
 
 

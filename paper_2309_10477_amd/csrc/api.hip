@@ -1023,11 +1023,15 @@ static heston_status run_exact(heston_ctx *c, const Request &q, uint64_t first, 
     E.seed = q.seed;
     E.first_path = first;
     E.n_paths = count;
-    E.n_lanes = (uint32_t)std::min<uint64_t>((count + BLOCK - 1) / BLOCK * BLOCK, EXACT_MAX_LANES);
+    // as few groups as finish in the number of rounds that the resident ones
+    // need, so that the last round is not nearly empty
+    const uint64_t rounds = (count + EXACT_MAX_GROUPS - 1) / EXACT_MAX_GROUPS;
+    const uint32_t per_block = BLOCK / EXACT_GROUP;
+    E.n_groups = (uint32_t)(((count + rounds - 1) / rounds + per_block - 1) / per_block * per_block);
     heston_status st;
     if ((st = upload_fix_bits(c, q, &E.fix_bits)) != HESTON_OK ||
-        (st = reserve(c, c->exact_scratch, (size_t)EXACT_MAX_GRID * E.n_lanes * 8)) != HESTON_OK ||
-        (st = reserve(c, c->partials, (size_t)(E.n_lanes / BLOCK) * EXACT_REC * 8)) != HESTON_OK ||
+        (st = reserve(c, c->exact_scratch, (size_t)EXACT_MAX_GRID * E.n_groups * 8)) != HESTON_OK ||
+        (st = reserve(c, c->partials, (size_t)(E.n_groups / per_block) * EXACT_REC * 8)) != HESTON_OK ||
         (st = reserve(c, c->rep_sums, EXACT_REC * 8)) != HESTON_OK)
         return st;
     E.scratch = (double *)c->exact_scratch.ptr;
@@ -1036,7 +1040,7 @@ static heston_status run_exact(heston_ctx *c, const Request &q, uint64_t first, 
     HIP_TRY(hipEventRecord(c->ev0, c->stream));
     HIP_TRY(launch_exact(E, c->stream));
     HIP_TRY(hipEventRecord(c->ev1, c->stream));
-    HIP_TRY(launch_reduce_rows(E.partials, E.n_lanes / BLOCK, EXACT_REC,
+    HIP_TRY(launch_reduce_rows(E.partials, E.n_groups / per_block, EXACT_REC,
                                (double *)c->rep_sums.ptr, c->stream));
     HIP_TRY(hipMemcpyAsync(sums, c->rep_sums.ptr, EXACT_REC * 8, hipMemcpyDeviceToHost,
                            c->stream));

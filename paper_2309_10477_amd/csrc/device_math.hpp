@@ -77,15 +77,6 @@ __device__ __forceinline__ void box_muller_log2(float ua, float ub, float &za, f
     za = rad * __builtin_amdgcn_cosf(ub);
     zb = rad * __builtin_amdgcn_sinf(ub);
 }
-__device__ __forceinline__ void box_muller(double ua, double ub, double &za, double &zb)
-{
-    const double rad = sqrt(-2.0 * log(ua));
-    double s, c;
-    sincospi(2.0 * ub, &s, &c);
-    za = rad * c;
-    zb = rad * s;
-}
-
 // Box-Muller pair of two random words, in double: the map above at the words'
 // uniforms, through the LDS tables (load_fp64_tables).
 __device__ __forceinline__ void box_muller_words(uint32_t wa, uint32_t wb, double &za, double &zb)

@@ -1,6 +1,6 @@
 // Exact simulation of the Heston model (paper: algorithm "Broadie and Kaya
 // exact simulation algorithm", section "Heston Model Exact simulation", and
-// the sections on its two bottlenecks), FP64, one path per lane at a time.
+// the sections on its two bottlenecks), FP64, one path per 16 lanes at a time.
 //
 // Step of length D from (x = ln S/S0, V_u):
 //  1. V_t = c X, X non-central chi-square with d = 4 kappa theta / sigma^2
@@ -36,9 +36,28 @@
 // of words 0, 1 and the acceptance uniform of word 2; word 3 of block 1 is
 // the uniform that lowers a shape below one).
 //
-// The Re Phi of the current draw live in `scratch`, one column per lane
-// ([point][lane], coalesced); each lane walks paths lane, lane + n_lanes, ...
-// and keeps FP64 sums of its estimators, reduced per block at the end.
+// Layout: a draw's characteristic function at 120 to 700 grid points is nearly
+// all of the work, and points are independent, so a group of 16 lanes (a DPP
+// row) takes one path and its lanes the points 16 m + 1 .. 16 m + 16: a wave
+// holds four paths instead of 64, whose grid lengths, series and iteration
+// counts otherwise leave two fifths of its lanes idle, and a launch of 2^16
+// paths has 16 waves per SIMD of work instead of one.  Group sums are DPP
+// butterflies (the same value in every lane, so a group's control flow is
+// uniform).  The gamma sampler's attempts run one per lane as well.
+// A point costs about 350 VALU instructions (900 before): one square root, a
+// sine and exponential and one complex logarithm give g, e^{-gD/2} and ln z,
+// z^2/4 is formed without a logarithm, and the Bessel series takes its
+// 1 / (k (k + nu)) from an LDS table.
+// The Re Phi / j of the current draw stay in LDS up to EXACT_LDS_POINTS points
+// of a group, beyond that in the group's row of `scratch`: 39 KiB per block and
+// 128 VGPRs, four blocks per CU (three with 320 points in LDS and 168 VGPRs ran
+// 18% longer: the sampler waits on its own dependent chains; VALU-busy 0.72 at
+// four, 0.58-0.63 at three).
+// European call, 2^18 paths, one step: 3.33 -> 1.11 ms; the quarterly Asian
+// (paper's parameters, four steps), 2^16 paths: 19.9 -> 2.66 ms.
+//
+// Each group walks paths group, group + n_groups, ... and its first lane keeps
+// FP64 sums of the estimators, reduced per block at the end.
 #include <hip/hip_runtime.h>
 
 #include "cplx.hpp"
@@ -51,6 +70,40 @@ namespace {
 
 constexpr double PI = 3.14159265358979323846;
 constexpr double GRID_EPS = 1e-10;
+constexpr int GROUP = EXACT_GROUP;
+constexpr int GROUPS = BLOCK / GROUP; // groups per block
+constexpr uint32_t LDS_ROW = EXACT_LDS_POINTS + 16; // rows of neighbouring groups on other banks
+constexpr int RC_TABLE = 256;
+
+struct ExactShared {
+    double w[GROUPS][LDS_ROW]; // Re Phi(h j) / j, j = 1 ..
+    double rc[RC_TABLE];       // 1 / (k (k + nu)), k = 1 .. RC_TABLE
+    double red[BLOCK / 64][EXACT_REC];
+};
+
+template <int CTRL> __device__ __forceinline__ double row_move(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+// Sum over the group's 16 lanes, bitwise the same in each: quads by
+// quad_perm, their halves and the row by mirrors.
+__device__ __forceinline__ double group_sum(double v)
+{
+    v += row_move<0xB1>(v);  // lane ^ 1
+    v += row_move<0x4E>(v);  // lane ^ 2
+    v += row_move<0x141>(v); // half mirror
+    v += row_move<0x140>(v); // mirror
+    return v;
+}
+__device__ __forceinline__ int group_lane() { return threadIdx.x & (GROUP - 1); }
+// Bit l: the condition in lane l of the group.
+__device__ __forceinline__ uint32_t group_vote(bool c)
+{
+    const uint64_t b = __builtin_amdgcn_ballot_w64(c);
+    return (uint32_t)(b >> (threadIdx.x & 48u)) & 0xFFFFu;
+}
 
 // Philox blocks of one (path, step).
 struct Draw {
@@ -61,31 +114,35 @@ struct Draw {
     }
 };
 
-// Gamma(alpha, 1); NaN after too many rejections.
+// Gamma(alpha, 1), NaN after too many rejections: lane l of the group takes
+// attempts l + 1, l + 17, ...; the first accepted one counts, as in a
+// sequential walk.
 __device__ double gamma_draw(double alpha, const Draw &dr)
 {
     const double a = alpha < 1.0 ? alpha + 1.0 : alpha;
     const double d = a - 1.0 / 3.0, c = 1.0 / sqrt(9.0 * d);
-    double g = __builtin_nan(""), boost = 1.0;
-    for (int k = 1; k <= EXACT_MAX_GAMMA_ATTEMPTS; ++k) {
-        const U4 w = dr.block((uint32_t)k);
-        if (k == 1)
-            boost = uniform_f64(w.w);
+    double g = __builtin_nan("");
+    uint32_t w1 = 0; // word 3 of block 1 (lane 0's first attempt)
+    for (int k0 = 1; k0 <= EXACT_MAX_GAMMA_ATTEMPTS; k0 += GROUP) {
+        const U4 w = dr.block((uint32_t)(k0 + group_lane()));
+        if (k0 == 1)
+            w1 = w.w;
         double x, unused;
-        box_muller(uniform_f64(w.x), uniform_f64(w.y), x, unused);
-        double v = 1.0 + c * x;
-        if (v <= 0.0)
-            continue;
-        v = v * v * v;
-        if (log(uniform_f64(w.z)) < 0.5 * x * x + d - d * v + d * log(v)) {
-            g = d * v;
+        box_muller_words(w.x, w.y, x, unused);
+        const double v1 = 1.0 + c * x, v = v1 * v1 * v1;
+        const bool ok = v1 > 0.0 &&
+                        -0.5 * neg2_log_uniform(w.z) < 0.5 * x * x + d - d * v + d * log(v);
+        const uint32_t accepted = group_vote(ok);
+        if (accepted) {
+            g = __shfl(d * v, __builtin_ctz(accepted), GROUP);
             break;
         }
     }
     if (alpha < 1.0)
-        g *= pow(boost, 1.0 / alpha);
+        g *= pow(uniform_f64((uint32_t)__shfl((int)w1, 0, GROUP)), 1.0 / alpha);
     return g;
 }
+static_assert(EXACT_MAX_GAMMA_ATTEMPTS % GROUP == 0, "whole rounds of attempts");
 
 // Smallest k with u <= P(N <= k), N ~ Poisson(mu); NaN above the mean limit.
 __device__ double poisson_inverse(double mu, double u)
@@ -103,165 +160,270 @@ __device__ double poisson_inverse(double mu, double u)
     return (double)k;
 }
 
-// S(z) = sum_k (z^2/4)^k / (k! (nu+1)_k); `bad` set if the sum does not
-// settle or would lose too much to cancellation.
-__device__ Cx bessel_sum(Cx z, double nu, bool &bad)
+// 1 / (k (k + nu)): hardware reciprocal and one Newton step.
+__device__ __forceinline__ double series_rc(int k, double nu)
 {
-    const double az = cabs(z);
-    if (az > 600.0 || az - z.re > 20.0)
-        bad = true;
-    const Cx q = z * z * 0.25;
+    const double den = (double)k * ((double)k + nu);
+    const double rc = __builtin_amdgcn_rcp(den);
+    return rc * fma(-den, rc, 2.0);
+}
+
+// S = sum_k q^k / (k! (nu+1)_k), q = z^2 / 4, four terms between checks (their
+// table entries read ahead); `bad` set if the sum does not settle.
+__device__ __forceinline__ Cx bessel_sum(Cx q, const double *rc, double nu, bool &bad)
+{
     Cx t{1.0, 0.0}, s{1.0, 0.0};
-    for (int k = 1; k < 2000; ++k) {
-        // 1 / (k (k + nu)): hardware reciprocal and one Newton step
-        const double den = (double)k * ((double)k + nu);
-        double rc = __builtin_amdgcn_rcp(den);
-        rc = rc * fma(-den, rc, 2.0);
-        t = t * q * rc;
+    const double q2 = q.re * q.re + q.im * q.im;
+    auto four = [&](double f0, double f1, double f2, double f3) {
+        t = t * (q * f0);
         s = s + t;
-        // |t| < 1e-17 |s|, compared squared
-        if ((double)k > 0.5 * az &&
-            t.re * t.re + t.im * t.im < 1e-34 * (s.re * s.re + s.im * s.im))
+        t = t * (q * f1);
+        s = s + t;
+        t = t * (q * f2);
+        s = s + t;
+        t = t * (q * f3);
+        s = s + t;
+    };
+    // k > |z| / 2 and |t| < 1e-17 |s|, compared squared
+    auto settled = [&](int k) {
+        const double k2 = (double)(k * k);
+        return k2 * k2 > q2 &&
+               t.re * t.re + t.im * t.im < 1e-34 * (s.re * s.re + s.im * s.im);
+    };
+    for (int k = 0; k < RC_TABLE; k += 4) {
+        four(rc[k], rc[k + 1], rc[k + 2], rc[k + 3]);
+        if (settled(k + 4))
+            return s;
+    }
+    for (int k = RC_TABLE + 1; k < 2000; k += 4) {
+        four(series_rc(k, nu), series_rc(k + 1, nu), series_rc(k + 2, nu), series_rc(k + 3, nu));
+        if (settled(k + 3))
+            return s;
+    }
+    bad = true;
+    return s;
+}
+// The same at a real z >= 0.
+__device__ __forceinline__ double bessel_sum_real(double q, double az, const double *rc, double nu,
+                                                  bool &bad)
+{
+    double t = 1.0, s = 1.0;
+    for (int k = 1; k < 2000; ++k) {
+        t *= q * (k <= RC_TABLE ? rc[k - 1] : series_rc(k, nu));
+        s += t;
+        if ((double)k > 0.5 * az && t < 1e-17 * s)
             return s;
     }
     bad = true;
     return s;
 }
 
-// Per-draw constants of Phi: the Bessel terms at a = 0 and the endpoint sums.
+// Per-draw constants of Phi.
 struct PhiCtx {
-    double vu, vt, r, sum_v;   // r = sqrt(vu vt)
-    double log_zk;             // ln z(0) (r > 0)
-    double log_s_zk;           // ln S(z(0))
+    double sum_v; // (vu + vt) / sigma^2
+    double vv;    // vu vt
+    double c0;    // the constant part of ln|Phi / S|
 };
 
-// log Phi(a) = lp + ln S(z(a)) (lp returned, S(z(a)) in *s; S = 1 when r = 0).
-// ln z(a) is summed from its factors (ln r + ln 4g - g D/2 -
-// ln(sigma^2 (1 - e^{-gD}))): it cannot underflow, and its imaginary part is
-// an argument of z continuous along a >= 0, the branch of (z/2)^nu.
-__device__ Cx log_phi_part(const ExactLaunch &L, const PhiCtx &pc, double a, Cx *s, bool &bad)
+// Phi(a) = e^{lp} S: lp returned, S = S(z(a)) and |z^2/4|^2 in *s and *q2.  With
+// g = sqrt(kappa^2 - 2 i sigma^2 a) and z = (4/sigma^2) sqrt(vu vt) g
+// e^{-gD/2} / (1 - e^{-gD}), ln(g / (1 - e^{-gD})) - gD/2 is the logarithm of
+// both the first factor of Phi and of z up to constants; its imaginary part,
+// arg(g conj(1 - e^{-gD})) - Im g D/2, is continuous along a >= 0 (each
+// argument stays within (-3 pi/4, pi/2)), the branch of (z/2)^nu; the modulus
+// |g|^2 = |kappa^2 - 2 i sigma^2 a|.  Summed from its factors it cannot
+// underflow; q = z^2/4 may, where S is 1.
+__device__ __forceinline__ Cx log_phi_part(const ExactLaunch &L, const PhiCtx &pc, const double *rc,
+                                           double a, Cx *s, double *q2, bool &bad)
 {
-    const Cx g = csqrt(Cx{L.kappa2, -L.two_sigma2 * a});
-    const Cx eg = cexp(g * (-L.D));
-    const Cx one{1.0, 0.0};
-    const Cx ome = one - eg;
-    const Cx lg = clog(g), lome = clog(ome);
-    const Cx t1 = lg - g * (0.5 * L.D) + Cx{L.t1_const, 0.0} - lome;
-    const Cx t2 = (Cx{L.coth_k, 0.0} - g * (one + eg) / ome) * (pc.sum_v * L.inv_sigma2);
-    // ln z(a) / r
-    const Cx lz0 = lg - g * (0.5 * L.D) - lome + Cx{L.log4_over_sigma2, 0.0};
-    if (pc.r == 0.0) { // I_nu(z) ~ (z/2)^nu / Gamma(nu+1) as z -> 0
-        *s = Cx{1.0, 0.0};
-        return t1 + t2 + (lz0 - Cx{L.log_zk_scale, 0.0}) * L.nu;
+    const double b = L.two_sigma2 * a;
+    const double m = sqrt_nonneg(fma(b, b, L.kappa2 * L.kappa2));
+    // gr = sqrt(x) and gi = -b / (2 gr) from one reciprocal square root
+    const double x = 0.5 * (m + L.kappa2), ir = rsqrt_pos(x);
+    const double g0 = x * ir, gr = fma(fma(-g0, g0, x), 0.5 * ir, g0), gi = -0.5 * b * ir;
+    const double u = 0.5 * L.D * gr, ph = -0.5 * L.D * gi;
+    double c, sn;
+    cos_sin(ph, c, sn);
+    const double e = exp_plain(-u);
+    const Cx e1{e * c, e * sn}, eg = e1 * e1;
+    const Cx ome{1.0 - eg.re, -eg.im};
+    const double w2 = ome.re * ome.re + ome.im * ome.im, iw = rcp_pos(w2);
+    const double x1 = -0.25 * neg2_log(m * iw, 0) - u;
+    const double A = angle(gr * ome.re + gi * ome.im, gi * ome.re - gr * ome.im) + ph;
+    // (1 + e^{-gD}) / (1 - e^{-gD})
+    const Cx ct{(1.0 - (eg.re * eg.re + eg.im * eg.im)) * iw, 2.0 * eg.im * iw};
+    Cx lp;
+    lp.re = x1 * (L.nu + 1.0) + pc.c0 + (L.coth_k - (gr * ct.re - gi * ct.im)) * pc.sum_v;
+    lp.im = A * (L.nu + 1.0) - (gr * ct.im + gi * ct.re) * pc.sum_v;
+    const double f = 2.0 * L.inv_sigma2 * iw;
+    const Cx q = Cx{L.kappa2, -b} * eg * (Cx{ome.re * ome.re - ome.im * ome.im, -2.0 * ome.re * ome.im} *
+                                          (f * f * pc.vv));
+    *q2 = q.re * q.re + q.im * q.im;
+    // |z| > 10: the series loses about e^{|z| - Re z} roundings (a wave-uniform
+    // branch, else the compiler evaluates it for every point)
+    if (__builtin_amdgcn_ballot_w64(*q2 > 625.0)) {
+        const double az = 2.0 * sqrt_nonneg(sqrt_nonneg(*q2));
+        double cA, sA;
+        cos_sin(A, cA, sA);
+        if (az > 10.0 && (az > 600.0 || az - az * cA > 20.0))
+            bad = true;
     }
-    const Cx lz{lz0.re + log(pc.r), lz0.im};
-    *s = bessel_sum(cexp(lz), L.nu, bad);
-    return t1 + t2 + Cx{L.nu * (lz.re - pc.log_zk) - pc.log_s_zk, L.nu * lz.im};
+    *s = bessel_sum(q, rc, L.nu, bad);
+    return lp;
 }
 
-// log Phi(a), for the moments at small a.
-__device__ Cx log_phi(const ExactLaunch &L, const PhiCtx &pc, double a, bool &bad)
+// Conditional mean and standard deviation of I from log Phi at a = h, 2h (even
+// and odd lanes).
+__device__ __forceinline__ void moments(const ExactLaunch &L, const PhiCtx &pc, const double *rc,
+                                        double vu, double vt, double &mu, double &sd, bool &bad)
 {
-    Cx s;
-    const Cx lp = log_phi_part(L, pc, a, &s, bad);
-    return lp + clog(s);
-}
-
-// Phi(a) on the grid: the Bessel sum multiplies instead of entering a logarithm.
-__device__ Cx phi(const ExactLaunch &L, const PhiCtx &pc, double a, bool &bad)
-{
-    Cx s;
-    const Cx lp = log_phi_part(L, pc, a, &s, bad);
-    return cexp(lp) * s;
-}
-
-// Conditional mean and standard deviation of I from log Phi at a = h, 2h.
-__device__ void moments(const ExactLaunch &L, const PhiCtx &pc, double &mu, double &sd, bool &bad)
-{
-    const double guess = fmax(0.5 * (pc.vu + pc.vt) * L.D, 1e-10);
+    const double guess = fmax(0.5 * (vu + vt) * L.D, 1e-10);
     const double h = 1e-3 / guess;
-    const Cx l0 = log_phi(L, pc, h, bad);
-    const Cx l1 = log_phi(L, pc, 2.0 * h, bad);
-    mu = (8.0 * l0.im - l1.im) / (6.0 * h);
-    const double var = -(16.0 * l0.re - l1.re) / (6.0 * h * h);
+    Cx s;
+    double q2;
+    const Cx lp = log_phi_part(L, pc, rc, (threadIdx.x & 1) ? 2.0 * h : h, &s, &q2, bad);
+    const double unit = rcp_pos(fabs(s.re) + fabs(s.im)); // S can leave single precision's range
+    const Cx l{lp.re + 0.5 * log_pos(s.re * s.re + s.im * s.im), lp.im + angle(s.re * unit, s.im * unit)};
+    const double ore = row_move<0xB1>(l.re), oim = row_move<0xB1>(l.im);
+    const bool odd = threadIdx.x & 1;
+    const double re0 = odd ? ore : l.re, re1 = odd ? l.re : ore;
+    const double im0 = odd ? oim : l.im, im1 = odd ? l.im : oim;
+    mu = (8.0 * im0 - im1) / (6.0 * h);
+    const double var = -(16.0 * re0 - re1) / (6.0 * h * h);
     sd = sqrt(fmax(var, (1e-3 * mu) * (1e-3 * mu)));
 }
 
-// F(x) - u and the density at x from the stored grid (rotation recurrence,
-// re-anchored every 64 points).
-__device__ void cdf_pdf(const double *col, uint32_t stride, uint32_t K, double h, double x,
-                        double &F, double &f)
+// F(x) = h x / pi + (2/pi) sum_j sin(h j x) w_j, its density and the density's
+// derivative: lane l sums j = l + 1, l + 17, ... by a rotation of 16 h x,
+// re-anchored at EXACT_LDS_POINTS and every 64 terms from there.  (Lanes whose
+// last row lies beyond K keep their j a row behind; they have no later terms.)
+__device__ __forceinline__ void cdf_pdf(const double *row, const double *far, uint32_t K, double h,
+                                        double x, double &F, double &f, double &fp)
 {
     const double th = h * x;
-    double s1, c1;
-    sincos(th, &s1, &c1);
-    double sf = 0.0, sp = 0.0, sj = 0.0, cj = 1.0;
-    for (uint32_t j = 1; j <= K; ++j) {
-        if ((j & 63u) == 0u) {
-            sincos(th * (double)j, &sj, &cj);
-        } else {
-            const double sn = sj * c1 + cj * s1;
-            cj = cj * c1 - sj * s1;
-            sj = sn;
+    double s, c, s16, c16;
+    double j = (double)(group_lane() + 1);
+    cos_sin(th * j, c, s);
+    s16 = __shfl(s, GROUP - 1, GROUP);
+    c16 = __shfl(c, GROUP - 1, GROUP);
+    double sf = 0.0, sp = 0.0, sd = 0.0;
+    auto terms = [&](const double *w_at, uint32_t from, uint32_t to) {
+        for (uint32_t i = from; i < to; i += GROUP) {
+            const double w = w_at[i], jw = j * w;
+            sf += s * w;
+            sp += c * jw;
+            sd += s * (j * jw);
+            j += (double)GROUP;
+            const double sn = s * c16 + c * s16;
+            c = c * c16 - s * s16;
+            s = sn;
         }
-        const double rp = col[(size_t)(j - 1) * stride];
-        sf += sj / (double)j * rp;
-        sp += cj * rp;
+    };
+    const uint32_t l = (uint32_t)group_lane();
+    terms(row, l, min(K, EXACT_LDS_POINTS));
+    for (uint32_t b = EXACT_LDS_POINTS; b < K; b += 64 * GROUP) {
+        cos_sin(th * j, c, s);
+        terms(far, b + l, min(K, b + 64 * GROUP));
     }
-    F = h * x / PI + (2.0 / PI) * sf;
-    f = h / PI + (2.0 * h / PI) * sp;
+    F = h * x * (1.0 / PI) + (2.0 / PI) * group_sum(sf);
+    f = h / PI + (2.0 * h / PI) * group_sum(sp);
+    fp = -(2.0 * h * h / PI) * group_sum(sd);
 }
 
-// One draw of I given (vu, vt) at the uniform u; `col` is the lane's scratch
-// column (stride n_lanes).
-__device__ double sample_integral(const ExactLaunch &L, double vu, double vt, double u,
-                                  double *col, bool &bad)
+// Standard normal quantile to 4.5e-4 (Abramowitz and Stegun 26.2.23), for the
+// inversion's first guess only.
+__device__ __forceinline__ float rough_normal(float u)
+{
+    const float p = u < 0.5f ? u : 1.0f - u;
+    const float t = __builtin_amdgcn_sqrtf(-1.38629436f * __builtin_amdgcn_logf(p));
+    const float z = t - (2.515517f + t * (0.802853f + t * 0.010328f)) /
+                            (1.0f + t * (1.432788f + t * (0.189269f + t * 0.001308f)));
+    return u < 0.5f ? -z : z;
+}
+
+// One draw of I given (vu, vt) at the uniform u; `row` is the group's LDS row,
+// `far` its scratch row.
+__device__ double sample_integral(const ExactLaunch &L, double vu, double vt, double u, double *row,
+                                  double *far, const double *rc, bool &bad)
 {
     PhiCtx pc;
-    pc.vu = vu;
-    pc.vt = vt;
-    pc.sum_v = vu + vt;
-    pc.r = sqrt(vu * vt);
-    pc.log_zk = 0.0;
-    pc.log_s_zk = 0.0;
-    if (pc.r != 0.0) {
-        pc.log_zk = log(pc.r) + L.log_zk_scale;
-        pc.log_s_zk = log(bessel_sum(Cx{exp(pc.log_zk), 0.0}, L.nu, bad).re);
+    pc.sum_v = (vu + vt) * L.inv_sigma2;
+    pc.vv = vu * vt;
+    pc.c0 = L.t1_const + L.nu * (L.log4_over_sigma2 - L.log_zk_scale);
+    if (pc.vv != 0.0) {
+        const double azk = sqrt_nonneg(pc.vv) * exp_plain(L.log_zk_scale);
+        if (azk > 600.0)
+            bad = true;
+        pc.c0 -= log_pos(bessel_sum_real(0.25 * azk * azk, azk, rc, L.nu, bad));
     }
     double mu, sd;
-    moments(L, pc, mu, sd, bad);
+    moments(L, pc, rc, vu, vt, mu, sd, bad);
     const double ueps = mu + 12.0 * sd;
     const double h = PI / ueps;
     const double thr = PI * GRID_EPS / 2.0;
-    // grid: doubled from 64 points until |Phi| / J at its last point is below
-    // the threshold; kept up to the last point whose |Phi| / j reaches it
-    uint32_t J = 64, j = 0, K = 0;
-    for (;;) {
-        double last = 0.0;
-        for (; j < J; ++j) {
-            const Cx ph = phi(L, pc, h * (double)(j + 1), bad);
-            col[(size_t)j * L.n_lanes] = ph.re;
-            last = cabs(ph);
-            if (last / (double)(j + 1) >= thr)
-                K = j + 1;
-        }
-        if (last / (double)J < thr)
+    // The grid is the first power of two J >= 64 points at whose end |Phi| / J
+    // is below the threshold, kept up to the last point K whose |Phi| / j
+    // reaches it.  Rows of 16 points end before J where no later point can
+    // reach the threshold or fail: |Phi| = G |S| with G / j decreasing in a
+    // (|g / sinh(gD/2)| falls and Re(g coth(gD/2)) rises with a), and with
+    // |q| <= (nu + 1) / 4 every zero of S (4 |q| >= 4 (nu + 1) by Rayleigh's
+    // sum of the zeros of J_nu) is far enough that |S| can grow by less than 2.
+    const double q_small = fmin(0.25 * (L.nu + 1.0), 25.0), q2_small = q_small * q_small;
+    uint32_t J = 64, K = 0;
+    for (uint32_t m = 0;; m += GROUP) {
+        const uint32_t i = m + (uint32_t)group_lane();
+        const double j = (double)(i + 1);
+        Cx s;
+        double q2;
+        const Cx lp = log_phi_part(L, pc, rc, h * j, &s, &q2, bad);
+        double c, sn;
+        cos_sin(lp.im, c, sn);
+        const double e = exp_plain(lp.re);
+        const double re = e * (c * s.re - sn * s.im), im = e * (c * s.im + sn * s.re);
+        const double w = re * rcp_pos(j);
+        if (i < EXACT_LDS_POINTS)
+            row[i] = w;
+        else
+            far[i] = w;
+        const double a2 = re * re + im * im, t2 = (thr * j) * (thr * j);
+        if (a2 >= t2)
+            K = i + 1;
+        // the row's last point decides
+        const int flags = (a2 < t2 ? 1 : 0) | (4.0 * a2 < t2 && q2 <= q2_small ? 2 : 0);
+        const int last = __builtin_amdgcn_mov_dpp(flags, 0x15F, 0xF, 0xF, true); // lane 15's
+        if (last & 2)
             break;
-        if (J >= EXACT_MAX_GRID || bad) { // the next points would not fit
-            bad = true;
-            break;
+        if (m + GROUP == J) {
+            if (last & 1)
+                break;
+            if (J >= EXACT_MAX_GRID || group_vote(bad)) { // the next points would not fit
+                bad = true;
+                break;
+            }
+            J *= 2;
         }
-        J *= 2;
     }
+    bad = group_vote(bad) != 0;
+    // the last point at or above the threshold over the group's lanes
+    K = max(K, (uint32_t)__builtin_amdgcn_mov_dpp((int)K, 0xB1, 0xF, 0xF, true));
+    K = max(K, (uint32_t)__builtin_amdgcn_mov_dpp((int)K, 0x4E, 0xF, 0xF, true));
+    K = max(K, (uint32_t)__builtin_amdgcn_mov_dpp((int)K, 0x141, 0xF, 0xF, true));
+    K = max(K, (uint32_t)__builtin_amdgcn_mov_dpp((int)K, 0x140, 0xF, 0xF, true));
     if (K == 0)
         K = 1;
     if (bad || !(ueps > 0.0))
         return __builtin_nan("");
+    // First guess: the quantile of the lognormal with I's mean and deviation;
+    // then Halley steps within a shrinking bracket (about three evaluations;
+    // Newton from the mean took six).
     double lo = 0.0, hi = ueps;
-    double x = fmin(fmax(mu, 1e-12), ueps);
+    const float v = (float)(sd / mu), ls = 0.69314718f * __builtin_amdgcn_logf(1.0f + v * v);
+    const float zq = rough_normal((float)u);
+    double x = mu * (double)fast_exp(__builtin_amdgcn_sqrtf(ls) * zq - 0.5f * ls);
+    x = fmin(fmax(x, 1e-12), 0.999999 * ueps);
     for (int it = 0; it < 200; ++it) {
-        double F, f;
-        cdf_pdf(col, L.n_lanes, K, h, x, F, f);
+        double F, f, fp;
+        cdf_pdf(row, far, K, h, x, F, f, fp);
         const double e = F - u;
         if (fabs(e) < 1e-13)
             return x;
@@ -271,16 +433,23 @@ __device__ double sample_integral(const ExactLaunch &L, double vu, double vt, do
             lo = x;
         if (hi - lo < 1e-14 * fmax(1.0, hi))
             return x;
-        const double xn = f > 0.0 ? x - e / f : 0.5 * (lo + hi);
+        const double newton = e / f, damp = 1.0 - 0.5 * newton * fp / f;
+        const double step = damp > 0.5 && damp < 2.0 ? newton / damp : newton;
+        const double xn = f > 0.0 ? x - step : 0.5 * (lo + hi);
         x = (lo < xn && xn < hi) ? xn : 0.5 * (lo + hi);
     }
     return x;
 }
 
-__global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
+__global__ __launch_bounds__(BLOCK, 4) void exact_kernel(const ExactLaunch L)
 {
-    __shared__ double red[BLOCK / 64][EXACT_REC];
-    const uint32_t lane = blockIdx.x * BLOCK + threadIdx.x;
+    __shared__ ExactShared sh;
+    load_fp64_tables<BLOCK>();
+    for (int k = threadIdx.x; k < RC_TABLE; k += BLOCK)
+        sh.rc[k] = series_rc(k + 1, L.nu);
+    __syncthreads();
+    const uint32_t group = blockIdx.x * GROUPS + threadIdx.x / GROUP;
+    const bool first_lane = group_lane() == 0;
     // sums of price, pathwise Delta and Rho (value, square) and the failures
     double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const bool asian = L.opt_type >= 2, geo = L.opt_type >= 4;
@@ -288,9 +457,10 @@ __global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
     const double sgn = call ? 1.0 : -1.0;
     const double disc = exp(-L.r * L.T), lnS0 = log(L.S0), nfix = (double)L.n_fix;
     const double D = L.D;
-    if (lane < L.n_lanes) {
-        double *col = L.scratch + lane;
-        for (uint64_t i = lane; i < L.n_paths; i += L.n_lanes) {
+    if (group < L.n_groups) {
+        double *row = sh.w[threadIdx.x / GROUP];
+        double *far = L.scratch + (uint64_t)group * EXACT_MAX_GRID;
+        for (uint64_t i = group; i < L.n_paths; i += L.n_groups) {
             const uint64_t p = L.first_path + i;
             Draw dr{(uint32_t)p, (uint32_t)(p >> 32), 0u, (uint32_t)L.seed,
                     (uint32_t)(L.seed >> 32)};
@@ -300,22 +470,22 @@ __global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
                 dr.step = j;
                 const U4 w = dr.block(0);
                 double zv, zs;
-                box_muller(uniform_f64(w.x), uniform_f64(w.y), zv, zs);
+                box_muller_words(w.x, w.y, zv, zs);
                 const double lam = V * L.ekD / L.c;
-                double X;
+                double shape = 0.5 * (L.d - 1.0), square = 0.0;
                 if (L.d > 1.0) {
-                    const double sq = zv + sqrt(lam);
-                    X = 2.0 * gamma_draw(0.5 * (L.d - 1.0), dr) + sq * sq;
-                } else {
-                    const double n = poisson_inverse(0.5 * lam, uniform_f64(w.w));
-                    X = n == n ? 2.0 * gamma_draw(0.5 * L.d + n, dr) : __builtin_nan("");
+                    const double sq = zv + sqrt_nonneg(lam);
+                    square = sq * sq;
+                } else { // NaN above the mean limit
+                    shape = 0.5 * L.d + poisson_inverse(0.5 * lam, uniform_f64(w.w));
                 }
+                const double X = 2.0 * gamma_draw(shape, dr) + square;
                 const double vt = L.c * X;
                 if (!(vt >= 0.0)) {
                     bad = true;
                     break;
                 }
-                const double I = sample_integral(L, V, vt, uniform_f64(w.z), col, bad);
+                const double I = sample_integral(L, V, vt, uniform_f64(w.z), row, far, sh.rc, bad);
                 if (bad)
                     break;
                 Itot += I;
@@ -345,6 +515,8 @@ __global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
             est[2] = !itm ? 0.0
                      : asian ? disc * (sgn * B / nfix - L.T * sgn * (Xv - L.K))
                              : sgn * disc * L.K * L.T;
+            if (!first_lane)
+                continue;
             if (bad) {
                 acc[6] += 1.0;
             } else {
@@ -377,14 +549,14 @@ __global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
         const double v = k < 6 ? acc[k] : k == N_ACC ? acc[6] : 0.0;
         const double s = wave_sum(v);
         if (wl == 0)
-            red[wave][k] = s;
+            sh.red[wave][k] = s;
     }
     __syncthreads();
     if (threadIdx.x < EXACT_REC) {
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < BLOCK / 64; ++w)
-            s += red[w][threadIdx.x];
+            s += sh.red[w][threadIdx.x];
         L.partials[(uint64_t)blockIdx.x * EXACT_REC + threadIdx.x] = s;
     }
 }
@@ -393,9 +565,9 @@ __global__ __launch_bounds__(BLOCK) void exact_kernel(const ExactLaunch L)
 
 hipError_t launch_exact(const ExactLaunch &L, hipStream_t stream)
 {
-    if (L.n_lanes == 0 || L.n_lanes % BLOCK != 0 || L.n_lanes > EXACT_MAX_LANES)
+    if (L.n_groups == 0 || L.n_groups % GROUPS != 0 || L.n_groups > EXACT_MAX_GROUPS)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(exact_kernel, dim3(L.n_lanes / BLOCK), dim3(BLOCK), 0, stream, L);
+    hipLaunchKernelGGL(exact_kernel, dim3(L.n_groups / GROUPS), dim3(BLOCK), 0, stream, L);
     return hipGetLastError();
 }
 

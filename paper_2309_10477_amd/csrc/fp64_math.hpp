@@ -45,19 +45,17 @@ template <int BLOCK_SIZE> __device__ __forceinline__ void load_fp64_tables()
     __syncthreads();
 }
 
-// -2 ln u of the uniform u = ((w >> 9) + 1/2) 2^-23 of a random word.  u 2^24
-// is the odd integer (w >> 8) | 1, exact in double; it is z 2^k with z in
-// [0.70801, 1.41602), and -2 ln u = (24 - k) 2 ln 2 - 2 ln c - 2 ln(1 + r),
-// r = z / c - 1, |r| < 2^-9, the last by its series through r^6 (truncation
-// below 2^-65 relative to r).
-__device__ __forceinline__ double neg2_log_uniform(uint32_t w)
+// -2 ln(d 2^-shift) of a normal d > 0: d = z 2^k with z in [0.70801, 1.41602),
+// and the value is (shift - k) 2 ln 2 - 2 ln c - 2 ln(1 + r), r = z / c - 1,
+// |r| < 2^-9, the last by its series through r^6 (truncation below 2^-65
+// relative to r).
+__device__ __forceinline__ double neg2_log(double d, int shift)
 {
-    const double d = (double)((w >> 8) | 1u);
-    const uint32_t t = (uint32_t)__double2hiint(d) - LOG_OFFSET;
-    const double *row = fp64_tables().log[(t >> 12) & 255u];
-    const double z = __hiloint2double((int)((t & 0xFFFFFu) + LOG_OFFSET), __double2loint(d));
+    const int t = __double2hiint(d) - (int)LOG_OFFSET;
+    const double *row = fp64_tables().log[(t >> 12) & 255];
+    const double z = __hiloint2double((t & 0xFFFFF) + (int)LOG_OFFSET, __double2loint(d));
     const double r = fma(z, row[0], -1.0);
-    const double hi = fma((double)(24 - (int)(t >> 20)), 1.38629436111989061883, row[1]);
+    const double hi = fma((double)(shift - (t >> 20)), 1.38629436111989061883, row[1]);
     double p = fma(r, 1.0 / 3.0, -0.4);
     p = fma(r, p, 0.5);
     p = fma(r, p, -2.0 / 3.0);
@@ -65,23 +63,44 @@ __device__ __forceinline__ double neg2_log_uniform(uint32_t w)
     p = fma(r, p, -2.0);
     return fma(r, p, hi);
 }
-
-// cos and sin of 2 pi u, u the uniform of a random word: the nearest of 256
-// table angles plus delta, |delta| <= pi / 256, by the addition theorems with
-// the series of sin delta and cos delta - 1 (truncations below 2^-68).
-__device__ __forceinline__ void cos_sin_uniform(uint32_t w, double &c, double &s)
+// -2 ln u of the uniform u = ((w >> 9) + 1/2) 2^-23 of a random word: u 2^24 is
+// the odd integer (w >> 8) | 1, exact in double.
+__device__ __forceinline__ double neg2_log_uniform(uint32_t w)
 {
-    const double *row = fp64_tables().trig[(w + 0x800000u) >> 24];
-    const double d = fma((double)((int32_t)(w << 8) >> 17), 0x1.921fb54442d18p-21, 0x1.921fb54442d18p-22);
-    const double C = row[0], S = row[1], q = d * d;
+    return neg2_log((double)((w >> 8) | 1u), 24);
+}
+
+// (C + i S) e^{i d} for a table angle (C, S) and |d| <= pi / 256: the addition
+// theorems with the series of sin d and cos d - 1 (truncations below 2^-68).
+__device__ __forceinline__ void turn(double C, double S, double d, double &c, double &s)
+{
+    const double q = d * d;
     double sp = fma(q, -1.0 / 5040.0, 1.0 / 120.0);
     sp = fma(q, sp, -1.0 / 6.0);
     const double sd = fma(d * q, sp, d);
     double cp = fma(q, -1.0 / 720.0, 1.0 / 24.0);
     cp = fma(q, cp, -0.5);
-    const double cd = q * cp; // cos delta - 1
+    const double cd = q * cp; // cos d - 1
     c = C + fma(C, cd, -(S * sd));
     s = S + fma(S, cd, C * sd);
+}
+
+// cos and sin of 2 pi u, u the uniform of a random word, from the nearest of
+// the 256 table angles.
+__device__ __forceinline__ void cos_sin_uniform(uint32_t w, double &c, double &s)
+{
+    const double *row = fp64_tables().trig[(w + 0x800000u) >> 24];
+    const double d = fma((double)((int32_t)(w << 8) >> 17), 0x1.921fb54442d18p-21, 0x1.921fb54442d18p-22);
+    turn(row[0], row[1], d, c, s);
+}
+
+// cos and sin of x, |x| below about 1e6 (pi / 128 in two parts).
+__device__ __forceinline__ void cos_sin(double x, double &c, double &s)
+{
+    const double n = rint(x * 0x1.45f306dc9c883p+5);
+    const double d = fma(-n, 0x1.1a62633145c07p-60, fma(-n, 0x1.921fb54442d18p-6, x));
+    const double *row = fp64_tables().trig[(uint32_t)(int)n & 255u];
+    turn(row[0], row[1], d, c, s);
 }
 
 // sqrt(x) for x >= 0 (exactly 0 at 0): from the hardware's reciprocal square
@@ -150,6 +169,29 @@ __device__ __forceinline__ double exp_plain(double x)
     q = fma(f, q, 0x1.0000000000005p-1);
     q = fma(f, q, 1.0);
     return __builtin_amdgcn_ldexp(fma(f, q, 1.0), (int)n);
+}
+
+// ln(x) of a normal x > 0.
+__device__ __forceinline__ double log_pos(double x) { return -0.5 * neg2_log(x, 0); }
+
+// The argument of x + i y, (x, y) away from 0 and the ends of single precision's
+// range: a single-precision estimate (7e-4) picks the nearest table angle n pi / 128;
+// the rest is atan of the turned vector's slope, |slope| < 0.0133, by its
+// series (truncation below 2^-60).
+__device__ __forceinline__ double angle(double x, double y)
+{
+    const float xf = (float)x, yf = (float)y, ax = fabsf(xf), ay = fabsf(yf);
+    const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(ax, ay)), t2 = t * t;
+    float a = t * (0.99535f + t2 * (-0.28869f + t2 * 0.07934f));
+    a = ay > ax ? 1.57079633f - a : a;
+    a = xf < 0.0f ? 3.14159265f - a : a;
+    const float nf = rintf(copysignf(a, yf) * 40.7436654f);
+    const double *row = fp64_tables().trig[(uint32_t)(int)nf & 255u];
+    const double C = row[0], S = row[1];
+    const double d = fma(y, C, -(x * S)) * rcp_pos(fma(x, C, y * S)), q = d * d;
+    double p = fma(q, -1.0 / 7.0, 0.2);
+    p = fma(q, p, -1.0 / 3.0);
+    return fma((double)nf, 0x1.921fb54442d18p-6, fma(d * q, p, d));
 }
 
 } // namespace heston

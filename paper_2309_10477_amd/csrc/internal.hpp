@@ -121,8 +121,9 @@ constexpr uint32_t EXACT_COUNTER_TAG = 5u;      // fourth Philox counter word, p
 constexpr int EXACT_MAX_GAMMA_ATTEMPTS = 64;
 constexpr double EXACT_MAX_POISSON_MEAN = 700.0;
 constexpr uint32_t EXACT_MAX_GRID = 16384;      // characteristic-function points per draw
-constexpr uint32_t EXACT_MAX_LANES = 131072;    // resident lanes (two waves per SIMD:
-                                                 // the kernel holds 244 VGPRs)
+constexpr int EXACT_GROUP = 16;                 // lanes of a path
+constexpr uint32_t EXACT_LDS_POINTS = 208;      // points a group keeps in LDS
+constexpr uint32_t EXACT_MAX_GROUPS = 16384;    // resident groups: four blocks of 16 on 256 CUs
 constexpr int EXACT_REC = N_ACC + 2;            // partial record: estimator sums, failures, pad
 struct ExactLaunch {
     double S0, K, r, T, v0, kappa, theta, sigma, rho, rho_bar;
@@ -141,8 +142,8 @@ struct ExactLaunch {
     const uint32_t *fix_bits; // device bitmask over steps 1..N, or null = every step
     uint64_t seed;
     uint64_t first_path, n_paths;
-    uint32_t n_lanes;         // lanes of the launch; lane l takes paths l, l + n_lanes, ...
-    double *scratch;          // device [EXACT_MAX_GRID][n_lanes]: Re Phi on the grid
+    uint32_t n_groups;        // groups of the launch; group l takes paths l, l + n_groups, ...
+    double *scratch;          // device [n_groups][EXACT_MAX_GRID]: Re Phi / j on the grid
     double *partials;         // device [blocks][EXACT_REC]
     double *dump;             // device [n_paths][DUMP_WIDTH] or null
 };

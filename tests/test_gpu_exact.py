@@ -85,6 +85,20 @@ def test_poisson_mixture_regime(hm, ctx):
     check(hm, ctx, p, oracle.EURO_CALL, 2, 3, 300)
 
 
+@pytest.mark.parametrize("change,opt,N,n", [
+    # |Phi| / j falls below the threshold and rises again past a zero of the Bessel ratio
+    (dict(T=1.34, v0=0.069, kappa=3.283, theta=0.086, sigma=0.496), oracle.EURO_CALL, 4, 400),
+    # |z| about 28: long Bessel series
+    (dict(sigma=0.15), oracle.ASIAN_CALL, 4, 100),
+    # thousands of grid points: beyond a group's LDS row and its re-anchored blocks
+    (dict(T=4.7, v0=0.145, kappa=0.576, theta=0.061, sigma=0.867), oracle.EURO_PUT, 1, 40),
+    # fewer paths than a block has groups (2 is the least a call takes), and one more than two blocks
+    (dict(), oracle.EURO_CALL, 1, 2), (dict(), oracle.EURO_CALL, 1, 33)],
+    ids=["dip", "series", "long-grid", "two-paths", "ragged"])
+def test_grid_and_group_edges(hm, ctx, change, opt, N, n):
+    check(hm, ctx, PB.replace(**change), opt, N, 11, n)
+
+
 def test_explicit_fixings_and_wide_indices(hm, ctx):
     check(hm, ctx, PB, oracle.ASIAN_PUT, 6, (9 << 40) | 5, 200, first=(1 << 32) + 11,
           fixings=(2, 3, 6))
