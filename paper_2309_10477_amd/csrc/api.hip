@@ -841,8 +841,6 @@ heston_status heston_ctx_destroy(heston_ctx *c)
     if (c->side) {
         (void)hipStreamSynchronize(c->side);
         (void)hipStreamDestroy(c->side);
-        (void)hipEventDestroy(c->fork);
-        (void)hipEventDestroy(c->join);
     }
     delete c;
     return HESTON_OK;
@@ -894,11 +892,13 @@ static heston_status geo_control_setup(heston_ctx *c, const Request &q, GeoContr
     g.dt = p.T / q.n_steps;
     g.n_fix = o.fixing_steps ? o.n_fixings : q.n_steps;
     heston_status st;
+    if (!c->side)
+        HIP_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
     if (o.fixing_steps) {
         if ((st = reserve(c, c->geo_steps, (size_t)o.n_fixings * 4)) != HESTON_OK)
             return st;
         HIP_TRY(hipMemcpyAsync(c->geo_steps.ptr, o.fixing_steps, (size_t)o.n_fixings * 4,
-                               hipMemcpyHostToDevice, c->stream));
+                               hipMemcpyHostToDevice, c->side));
         g.steps = (const uint32_t *)c->geo_steps.ptr;
     }
     // First integration range: where a normal ln G with the variance of the
@@ -931,12 +931,10 @@ static heston_status geo_control_setup(heston_ctx *c, const Request &q, GeoContr
     if ((st = reserve(c, c->geo_buf, GEO_BUF_DOUBLES * 8)) != HESTON_OK ||
         (st = reserve(c, c->geo_partials, (size_t)geo_node_blocks() * 8)) != HESTON_OK)
         return st;
-    if (!c->host_geo)
-        HIP_TRY(hipHostMalloc((void **)&c->host_geo, 2 * sizeof(double)));
-    if (!c->side) {
-        HIP_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-        HIP_TRY(hipEventCreateWithFlags(&c->fork, hipEventDisableTiming));
-        HIP_TRY(hipEventCreateWithFlags(&c->join, hipEventDisableTiming));
+    if (!c->host_geo_dev) {
+        if (!c->host_geo)
+            HIP_TRY(hipHostMalloc((void **)&c->host_geo, 2 * sizeof(double)));
+        HIP_TRY(hipHostGetDevicePointer((void **)&c->host_geo_dev, c->host_geo, 0));
     }
     return HESTON_OK;
 }
@@ -1118,35 +1116,36 @@ static heston_status price_greeks_impl(heston_ctx *c, const heston_params *param
     GeoControl gc;
     if (L.cv) {
         // the control's price (latency-bound, few waves) runs on the side
-        // stream while the path kernel fills the device
+        // stream while the path kernel fills the device.  Its inputs are the
+        // request and its buffers are used on the side stream alone, and the
+        // call waits for both streams, so no event ties them together (a fork
+        // and a join event cost 10 us of a 270 us call).
         if ((st = geo_control_setup(c, q, gc)) != HESTON_OK)
             return st;
-        HIP_TRY(hipEventRecord(c->fork, c->stream));
-        HIP_TRY(hipStreamWaitEvent(c->side, c->fork, 0));
-        HIP_TRY(launch_geo_price_fixed(gc, (double *)c->geo_partials.ptr,
+        HIP_TRY(launch_geo_nodes_fixed(gc, (double *)c->geo_partials.ptr,
                                        (double *)c->geo_buf.ptr, c->side));
-        HIP_TRY(hipEventRecord(c->join, c->side));
     }
     HIP_TRY(hipEventRecord(c->ev0, c->stream));
     HIP_TRY(launch_paths(L, c->stream));
     HIP_TRY(hipEventRecord(c->ev1, c->stream));
     // the last reduction level writes the sums into the pinned host buffer
-    // (no copy launch); the host reads them after the stream synchronises
-    HIP_TRY(launch_reduce(L, c->host_sums_dev, c->stream));
-    double *geo_out = c->host_geo; // pinned (set up with the control)
+    // (no copy launch); the host reads them after the stream synchronises;
+    // the control's prices come the same way, its last launch issued after the
+    // path kernel's so that the path kernel starts sooner
+    const double *geo_out = c->host_geo; // pinned (set up with the control)
     if (L.cv) {
-        HIP_TRY(hipStreamWaitEvent(c->stream, c->join, 0));
-        HIP_TRY(hipMemcpyAsync(geo_out, (double *)c->geo_buf.ptr + GEO_OUT, 2 * sizeof(double),
-                               hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(launch_geo_finish_fixed(gc, (double *)c->geo_partials.ptr, (double *)c->geo_buf.ptr,
+                                        c->host_geo_dev, c->side));
     }
+    HIP_TRY(launch_reduce(L, c->host_sums_dev, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    if (L.cv)
+        HIP_TRY(hipStreamSynchronize(c->side));
     if (L.cv && !(std::isfinite(geo_out[0]) && std::isfinite(geo_out[1]))) {
         // the transform had not decayed by the end of the fixed range: search
         HIP_TRY(launch_geo_price_search(gc, (double *)c->geo_partials.ptr,
-                                        (double *)c->geo_buf.ptr, c->stream));
-        HIP_TRY(hipMemcpyAsync(geo_out, (double *)c->geo_buf.ptr + GEO_OUT, 2 * sizeof(double),
-                               hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
+                                        (double *)c->geo_buf.ptr, c->host_geo_dev, c->side));
+        HIP_TRY(hipStreamSynchronize(c->side));
     }
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, c->ev0, c->ev1));

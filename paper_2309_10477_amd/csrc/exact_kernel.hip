@@ -282,8 +282,7 @@ __device__ __forceinline__ void moments(const ExactLaunch &L, const PhiCtx &pc, 
     Cx s;
     double q2;
     const Cx lp = log_phi_part(L, pc, rc, (threadIdx.x & 1) ? 2.0 * h : h, &s, &q2, bad);
-    const double unit = rcp_pos(fabs(s.re) + fabs(s.im)); // S can leave single precision's range
-    const Cx l{lp.re + 0.5 * log_pos(s.re * s.re + s.im * s.im), lp.im + angle(s.re * unit, s.im * unit)};
+    const Cx l{lp.re + 0.5 * log_pos(s.re * s.re + s.im * s.im), lp.im + angle_scaled(s.re, s.im)};
     const double ore = row_move<0xB1>(l.re), oim = row_move<0xB1>(l.im);
     const bool odd = threadIdx.x & 1;
     const double re0 = odd ? ore : l.re, re1 = odd ? l.re : ore;

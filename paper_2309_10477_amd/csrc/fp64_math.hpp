@@ -193,5 +193,11 @@ __device__ __forceinline__ double angle(double x, double y)
     p = fma(q, p, -1.0 / 3.0);
     return fma((double)nf, 0x1.921fb54442d18p-6, fma(d * q, p, d));
 }
+// The same for any normal (x, y) away from 0, first scaled to |x| + |y| = 1.
+__device__ __forceinline__ double angle_scaled(double x, double y)
+{
+    const double f = rcp_pos(fabs(x) + fabs(y));
+    return angle(x * f, y * f);
+}
 
 } // namespace heston

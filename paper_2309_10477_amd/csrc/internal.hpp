@@ -270,10 +270,14 @@ constexpr int GEO_OUT = 2 * GEO_BOUND_POINTS;
 constexpr int GEO_BUF_DOUBLES = GEO_OUT + 6;
 constexpr uint32_t GEO_MAX_FIXED_RANGE = 4096;
 uint32_t geo_node_blocks();
-hipError_t launch_geo_price_fixed(const GeoControl &g, double *partials, double *buf,
+// The fixed range in two launches, so that the caller can start other work
+// between them; the call and put price go to `prices` (device-visible).
+hipError_t launch_geo_nodes_fixed(const GeoControl &g, double *partials, double *buf,
                                   hipStream_t stream);
+hipError_t launch_geo_finish_fixed(const GeoControl &g, double *partials, double *buf,
+                                   double *prices, hipStream_t stream);
 hipError_t launch_geo_price_search(const GeoControl &g, double *partials, double *buf,
-                                   hipStream_t stream);
+                                   double *prices, hipStream_t stream);
 
 // Fills the [N][STEP_WEIGHTS] fixing weights of `L` (its precision) at
 // L.step_weights.

@@ -179,6 +179,17 @@ def test_control_mean_across_parameters(hm, ctx, p):
                                              rel=1e-9)
 
 
+@pytest.mark.parametrize("N", [1, 7, 9, 63, 64, 65, 129])
+def test_control_mean_at_the_edges_of_its_chunks(hm, ctx, N):
+    """The transform goes through the dates 64 at a time and 8 to an unrolled
+    group: one date, either side of a group, of a chunk and of two chunks."""
+    opts = hm.Options(precision=1, control_variate=hm.CONTROL_GEOMETRIC,
+                      greeks=hm.GREEKS_PATHWISE)
+    r = ctx.price_greeks(PB.__dict__, oracle.ASIAN_PUT, 256, N, 3, opts)
+    assert r["cv_mean"] == pytest.approx(oracle.geometric_control_mean(PB, oracle.ASIAN_PUT, N, None),
+                                         rel=1e-9)
+
+
 def test_full_size_variance_reduction_and_agreement(hm, ctx):
     """2^20 paths x 252 daily fixings, FP32: the control cuts the standard
     error at least fivefold and the two estimates agree within their errors."""
