@@ -342,7 +342,9 @@ bool split_layout(const Request &q, const PriceLaunch &L, uint64_t count)
 {
     return q.o.precision == HESTON_FP64 && L.rng == HESTON_RNG_PHILOX && L.bumps && !L.cv &&
            (L.scheme == 0 || L.scheme == 1) && q.type <= HESTON_ASIAN_PUT &&
-           count <= (q.type >= HESTON_ASIAN_CALL ? SPLIT_MAX_PATHS_ASIAN : SPLIT_MAX_PATHS_EURO);
+           count <= (q.type >= HESTON_ASIAN_CALL && 2ull * L.n_fix > L.n_steps
+                         ? SPLIT_MAX_PATHS_DENSE
+                         : SPLIT_MAX_PATHS);
 }
 // Paths per block of the launch.
 uint64_t paths_per_block(const PriceLaunch &L)

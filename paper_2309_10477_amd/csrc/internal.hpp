@@ -31,15 +31,19 @@ constexpr int BLOCK = 256;         // threads per block of the path kernels
 constexpr int MAX_BRIDGE_DEPTH = 24;
 // Fourth Philox counter word of the QE scheme's per-step block.
 constexpr uint32_t QE_COUNTER_TAG = 4u;
+// Scenario-split layout of small FP64 bump launches (price_kernel SPLIT): paths
+// per wave, and the largest launches it is used for, the last whole number of
+// waves per SIMD (12288 paths each) at which it beats the fused layout.  Path
+// kernel at 100 steps, split against fused: European 32768 paths 38 / 43 us,
+// 49152 49 / 43 us; Asian fixing at every step 49152 70 / 78, 65536 109 / 78;
+// with four or thirteen dates 32768 44 / 50 and 47 / 53, 49152 55 / 51 and
+// 57 / 53.  (A fused Asian step is longer by five exponentials, so its one wave
+// per SIMD lasts longer.)
+constexpr uint32_t SPLIT_PATHS_PER_WAVE = 12;
+constexpr uint64_t SPLIT_MAX_PATHS = 36864;
+constexpr uint64_t SPLIT_MAX_PATHS_DENSE = 49152; // Asian, more than half of the steps fix
 // Largest per-block Sobol table (ceil(M/64) x 2N words) built for a launch;
 // above it the kernel combines the high direction numbers itself.
-// Scenario-split layout of small FP64 bump launches (price_kernel SPLIT):
-// paths per wave, and the largest launches it is used for, measured crossovers
-// with the fused layout at 100 steps: about three waves per SIMD for European
-// payoffs, eight for arithmetic Asians (whose fixings lengthen the fused step).
-constexpr uint32_t SPLIT_PATHS_PER_WAVE = 12;
-constexpr uint64_t SPLIT_MAX_PATHS_EURO = 36864;
-constexpr uint64_t SPLIT_MAX_PATHS_ASIAN = 98304;
 constexpr uint64_t SOBOL_HI_MAX_BYTES = 256ull << 20;
 // Fixing weights per step j (fixing time t = (j+1) dt): e^{rt}, t e^{rt},
 // t^2 e^{rt}, t^3 e^{rt} on the base grid, e^{rt} on the T + hT and T - hT grids.

@@ -177,6 +177,34 @@ def test_fp64_bump_estimates_at_layout_limit(hm, ctx, opt_type, n):
     _estimates_match(r, oracle.price_greeks(PB, opt_type, n, N, seed, threads=8))
 
 
+@pytest.mark.parametrize("N,fixings", [
+    (75, (1, 31, 32, 33, 63, 64, 65, 75)), (64, (32, 64)), (33, (1, 2, 33)),
+    (10, None), (11, None), (75, None)],
+    ids=["words", "word-ends", "half", "group", "group-and-one", "dense"])
+@pytest.mark.parametrize("scheme,mode", [(0, oracle.FULL_TRUNC), (1, oracle.ABSORB)])
+def test_fp64_fixing_flags_in_groups(hm, ctx, N, fixings, scheme, mode):
+    """The FP64 loops read the fixing flags of ten (one scenario per lane) or
+    two (fused) steps at once: dates on both sides of the 32-bit words and of
+    the groups, none, and every step, by the estimates of the one layout and
+    the per-path records of the other."""
+    n, seed = 500, 5
+    opts = hm.Options(scheme=scheme, fixings=fixings)
+    r = ctx.price_greeks(PB.__dict__, hm.ASIAN_CALL, n, N, seed, opts)
+    _estimates_match(r, oracle.price_greeks(PB, hm.ASIAN_CALL, n, N, seed, mode=mode,
+                                            fixings=fixings, threads=8))
+    d = dump(hm, ctx, PB, hm.ASIAN_CALL, n, N, seed, 0, n, opts)
+    check_records(d, PB, hm.ASIAN_CALL, N, seed, 0, n, 0, scheme, fixings, True)
+
+
+@pytest.mark.parametrize("n,fixings", [(49152, None), (49153, None), (36864, (3, 6)), (36865, (3, 6))])
+def test_fp64_asian_estimates_at_layout_limits(hm, ctx, n, fixings):
+    """Either side of the largest Asian counts laid out one scenario per lane,
+    with every step and with a third of the steps fixing."""
+    N, seed = 6, 78
+    r = ctx.price_greeks(PB.__dict__, 2, n, N, seed, hm.Options(fixings=fixings))
+    _estimates_match(r, oracle.price_greeks(PB, 2, n, N, seed, fixings=fixings, threads=8))
+
+
 @pytest.mark.parametrize("opt_type", [0, 1, 2, 3])
 def test_fp32_all_types(hm, ctx, opt_type):
     n, N, seed = 4096 + 100, 63, 7
