@@ -43,8 +43,9 @@ __device__ __forceinline__ void run_unit_paths(const BatchOption &op, uint64_t c
             __threadfence_block();
             adjoint_path_qe<R, ASIAN, BATCH_CKPT_EVERY>(op.k, p, scratch, BLOCK, tid, out);
         } else {
-            forward_path<R, ASIAN, SC == 0>(op.k, p, x, v, A, B, scratch, BLOCK, tid,
-                                            BATCH_CKPT_EVERY);
+            // (batched Asians fix at every step)
+            forward_steps<R, ASIAN, SC == 0, true>(op.k, p, x, v, A, B, scratch, BLOCK, tid,
+                                                   BATCH_CKPT_EVERY);
             __threadfence_block();
             adjoint_path<R, ASIAN, SC == 0, BATCH_CKPT_EVERY>(op.k, p, scratch, BLOCK, tid, out);
         }
@@ -53,7 +54,7 @@ __device__ __forceinline__ void run_unit_paths(const BatchOption &op, uint64_t c
         if constexpr (SC == 2)
             forward_path_qe<R, ASIAN>(op.k, p, x, v, A, B, nullptr, 0, 0, 2);
         else
-            forward_path<R, ASIAN, SC == 0>(op.k, p, x, v, A, B, nullptr, 0, 0, 2);
+            forward_steps<R, ASIAN, SC == 0, true>(op.k, p, x, v, A, B, (R *)nullptr, 0, 0, 2);
         path_estimators<ASIAN>(op.k, (double)x, (double)A, (double)B, out[0], out[1], out[2]);
 #pragma unroll
         for (int e = 3; e < 8; ++e)

@@ -97,6 +97,17 @@ def test_adjoint_fp64_matches_tangent(hm, ctx, opt_type, scheme):
         assert grads[k][1] == pytest.approx(se, rel=1e-6, abs=1e-12)
 
 
+@pytest.mark.parametrize("scheme", [0, 1])
+@pytest.mark.parametrize("N,every,fix", [
+    (1, 8, (1,)), (31, 8, (31,)), (32, 16, (1, 32)), (33, 8, (31, 32, 33)),
+    (65, 16, (15, 16, 17, 31, 32, 48, 63, 64, 65)), (65, 16, None)])
+def test_adjoint_fixing_flags_of_a_segment(hm, ctx, N, every, fix, scheme):
+    """Fixing dates at the edges of the flag words and of the checkpoint
+    segments, sparse and at every step, with an odd last step."""
+    _, _, d = adjoint_per_path(hm, ctx, PB, 2, 300, N, 3, 0, every, scheme, fix)
+    check_against_tangent(d, PB, 2, N, 3, 0, 300, 0, scheme, fix)
+
+
 @pytest.mark.parametrize("every", [8, 16])
 @pytest.mark.parametrize("opt_type", [0, 2])
 def test_adjoint_fp32_matches_tangent(hm, ctx, every, opt_type):
