@@ -177,16 +177,15 @@ __device__ __forceinline__ void scaled_step_fix(R &y, R &w, const Grid<R> &g, R 
 
 // Andersen's quadratic-exponential (QE) scheme on one time grid, in the same
 // scaled state (y = ln(S/S0)/ln 2 without the drift r t, w = V dt).  With
-// E = e^{-kappa dt}, the square-root process's conditional mean and variance
-// of w' = V(t+dt) dt given w are m = E w + theta dt (1-E) and
-// s2 = cs1 w + cs0, cs1 = sigma^2 dt E (1-E) / kappa,
-// cs0 = theta sigma^2 dt^2 (1-E)^2 / (2 kappa); the log-price step is
-// (K0 + K1 V + K2 V' + sqrt(K3 V + K4 V') Zs) / ln 2 with Andersen's central
+// E = e^{-kappa dt}, the square-root process's conditional mean and half its
+// variance of w' = V(t+dt) dt given w are m = E w + theta dt (1-E) and
+// h = h1 w + h0, 2 h1 = sigma^2 dt E (1-E) / kappa,
+// 2 h0 = theta sigma^2 dt^2 (1-E)^2 / (2 kappa); the log-price step is
+// (K0 + K1 V + K2 V' + sqrt(K3 (V + V')) Zs) / ln 2 with Andersen's central
 // weights gamma1 = gamma2 = 1/2, here k0 = K0/ln 2, k1 = K1/(dt ln 2),
-// k2 = K2/(dt ln 2), k3 = K3/dt, k4 = K4/dt (the 1/ln 2 of the diffusion term
-// rides on Zs).
+// k2 = K2/(dt ln 2) and sqrt(w + w') z, z = sqrt((1 - rho^2)/2) Zs / ln 2.
 template <class R> struct QEGrid {
-    R E, mth, cs1, cs0, k0, k1, k2, k3, k4;
+    R E, mth, h1, h0, k0, k1, k2;
 };
 
 template <class R> __device__ __forceinline__ QEGrid<R> qe_grid(const StepCoef &c, const PriceLaunch &L)
@@ -196,13 +195,11 @@ template <class R> __device__ __forceinline__ QEGrid<R> qe_grid(const StepCoef &
     QEGrid<R> g;
     g.E = (R)E;
     g.mth = (R)(L.theta * dt * (1.0 - E));
-    g.cs1 = (R)(s2s * dt * E * (1.0 - E) / L.kappa);
-    g.cs0 = (R)(L.theta * s2s * dt * dt * (1.0 - E) * (1.0 - E) / (2.0 * L.kappa));
+    g.h1 = (R)(0.5 * (s2s * dt * E * (1.0 - E) / L.kappa));
+    g.h0 = (R)(0.5 * (L.theta * s2s * dt * dt * (1.0 - E) * (1.0 - E) / (2.0 * L.kappa)));
     g.k0 = (R)(-L.rho * L.kappa * L.theta * dt / L.sigma * LOG2E);
     g.k1 = (R)((0.5 * dt * kr - L.rho / L.sigma) / dt * LOG2E);
     g.k2 = (R)((0.5 * dt * kr + L.rho / L.sigma) / dt * LOG2E);
-    g.k3 = (R)(0.5 * (1.0 - L.rho * L.rho));
-    g.k4 = g.k3;
     return g;
 }
 
@@ -211,55 +208,60 @@ __device__ __forceinline__ double fast_log(double x) { return log(x); }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double fast_rcp(double x) { return rcp_pos(x); }
 
-// One QE step of one scenario, in two parts; z1l = Zs / ln 2, zv the normal
-// of the quadratic branch, uv the uniform of the exponential branch.
-// psi = s2 / m^2 <= 3/2 takes the scaled squared normal a (b + zv)^2, else V'
-// is 0 with probability p = (psi-1)/(psi+1) and exponential above it.
-// qe_pre gives m, s2 and the branch (psi <= 3/2 tested as s2 <= 3/2 m^2, no
-// division); qe_post evaluates a branch only when some lane of the wave takes
-// it (quad, expo: wave-uniform votes over all scenarios), psi itself only in
-// the exponential branch.
-// Away from zero variance every lane takes the quadratic branch, so whole
-// waves skip the exponential one and its logarithm; each lane still selects
-// by its own psi, so the result is that of evaluating both.
+// The variance step of one scenario, in parts; zv the normal of the quadratic
+// branch, uv the uniform of the exponential one.  psi = 2 h / m^2 <= 3/2 takes
+// the scaled squared normal a (b + zv)^2, else V' is 0 with probability p =
+// (psi-1)/(psi+1) and exponential above it.
+// qe_pre gives m, m^2, h and the branch (psi <= 3/2 tested as h <= 3/4 m^2, no
+// division).  Near zero variance the scheme amplifies a change of rounding in
+// V', so its arithmetic is kept to single roundings of psi, b^2, b and a; half
+// the variance instead of the variance saves the factors 2 without a rounding.
 template <class R> struct QEPre {
-    R m, s2;
-    bool quad; // psi = s2 / m^2 <= 3/2
+    R m, mm, h;
+    bool quad; // psi = 2 h / m^2 <= 3/2
 };
 
 template <class R> __device__ __forceinline__ QEPre<R> qe_pre(R w, const QEGrid<R> &g)
 {
     const R m = w * g.E + g.mth;
-    const R s2 = w * g.cs1 + g.cs0;
-    return QEPre<R>{m, s2, s2 <= R(1.5) * (m * m)};
+    const R h = w * g.h1 + g.h0;
+    const R mm = m * m;
+    return QEPre<R>{m, mm, h, h <= R(0.75) * mm};
 }
-
-template <class R>
-__device__ __forceinline__ void qe_post(R &y, R &w, const QEGrid<R> &g, const QEPre<R> &q, R z1l,
-                                        R zv, R uv, bool quad, bool expo)
+template <class R> __device__ __forceinline__ R add_rounded(R a, R b)
 {
-    const R m = q.m, s2 = q.s2;
-    R wq = R(0), we = R(0);
-    if (quad) {
-        const R inv = R(2) * m * m * fast_rcp(s2);
-        const R b2 = inv - R(1) + fast_sqrt(inv * (inv - R(1)));
-        const R b = fast_sqrt(b2);
-        const R a = m * fast_rcp(R(1) + b2);
-        const R bz = b + zv;
-        wq = a * bz * bz;
-    }
-    if (expo) {
-        // p = (psi - 1) / (psi + 1), 1 - p = 2 / (psi + 1), 1 / beta = m (psi + 1) / 2;
-        // uv <= p is tested as uv (psi + 1) <= psi - 1 and ln((1 - p) / (1 - uv))
-        // as -ln((psi + 1)(1 - uv) / 2)
-        const R rm = fast_rcp(m);
-        const R psi = s2 * rm * rm;
-        const R pp1 = psi + R(1);
-        we = uv * pp1 <= psi - R(1) ? R(0)
-                                    : -(R(0.5) * m * pp1) * fast_log(R(0.5) * pp1 * (R(1) - uv));
-    }
-    const R wn = q.quad ? wq : we;
-    y = y + g.k0 + g.k1 * w + g.k2 * wn + fast_sqrt(g.k3 * w + g.k4 * wn) * z1l;
+#pragma clang fp contract(off)
+    return a + b;
+}
+// ROUND_ZV: zv enters as a rounded value (five scenarios share it), not as the
+// product of a fused multiply-add.
+template <class R, bool ROUND_ZV> __device__ __forceinline__ R qe_quad(const QEPre<R> &q, R zv)
+{
+    const R inv = q.mm * fast_rcp(q.h); // 2 / psi
+    const R b2 = inv - R(1) + fast_sqrt(inv * (inv - R(1)));
+    const R a = q.m * fast_rcp(R(1) + b2);
+    const R b = fast_sqrt(b2);
+    const R bz = ROUND_ZV ? add_rounded(b, zv) : b + zv;
+    return a * bz * bz;
+}
+template <class R> __device__ __forceinline__ R qe_expo(const QEPre<R> &q, R uv)
+{
+    // p = (psi - 1) / (psi + 1), 1 - p = 2 / (psi + 1), 1 / beta = m (psi + 1) / 2;
+    // uv <= p is tested as uv (psi + 1) <= psi - 1 and ln((1 - p) / (1 - uv))
+    // as -ln((psi + 1)(1 - uv) / 2)
+    const R rm = fast_rcp(q.m);
+    const R psi = (q.h + q.h) * rm * rm;
+    const R pp1 = psi + R(1);
+    return uv * pp1 <= psi - R(1)
+               ? R(0)
+               : -(R(0.5) * q.m * pp1) * fast_log(R(0.5) * pp1 * (R(1) - uv));
+}
+// The log-price step from w to wn; then w = wn.
+template <class R>
+__device__ __forceinline__ void qe_price(R &y, R &w, R wn, const QEGrid<R> &g, R z)
+{
+    y = y + g.k0 + g.k1 * w + g.k2 * wn;
+    y = y + fast_sqrt(w + wn) * z;
     w = wn;
 }
 
@@ -270,9 +272,10 @@ __device__ __forceinline__ bool any_lane(bool c)
     return __builtin_amdgcn_ballot_w64(c) != 0u;
 }
 
-// Single-precision QE asks for six waves per SIMD: left to itself the compiler
-// spends 140-147 VGPRs on it (three waves); bounded, it fits in 76 without
-// spilling and runs 4% faster.  The other variants keep the default.
+// Single-precision QE asks for four waves per SIMD or more: it is bound by issue
+// (five scenarios' 34 transcendentals and about 150 plain instructions a step),
+// and the bound only steers the schedule (1326 us at 2^20 x 252; asked for six
+// 1338, five 1332, nothing 1338).  The other variants keep the default.
 // SPLIT (small FP64 launches with fused bumps, Milstein, Philox, European or
 // arithmetic Asian): each lane runs one scenario of one path -- lane l of a
 // wave takes path l / 5 of the wave's SPLIT_PATHS_PER_WAVE and scenario l % 5
@@ -285,7 +288,7 @@ __device__ __forceinline__ bool any_lane(bool c)
 // instructions per path, which pays while the launch has few waves per SIMD.
 template <class R, int RNG, int AV, bool BUMPS, int SCH, bool SPLIT = false>
 __global__ __launch_bounds__(BLOCK)
-__attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 6 : 1))) void price_kernel(
+__attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 4 : 1))) void price_kernel(
     const PriceLaunch L)
 {
     static_assert(!SPLIT || (sizeof(R) == 8 && RNG == 0 && BUMPS && (AV == 0 || AV == 1) &&
@@ -472,6 +475,7 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 6 : 1))) void pr
         // give the Box-Muller pair (Zs, Zv), word 2 the uniform Uv.
         const uint32_t k0 = (uint32_t)L.seed, k1 = (uint32_t)(L.seed >> 32);
         const uint32_t plo = (uint32_t)p, phi = L.wide_paths ? (uint32_t)(p >> 32) : 0u;
+        const R qe_z = (R)(LOG2E * sqrt(0.5 * (1.0 - L.rho * L.rho)));
         for (uint32_t j = 0; j < N; ++j) {
             const U4 q = philox4x32_10(U4{j, plo, phi, QE_COUNTER_TAG}, k0, k1);
             R zs, zv;
@@ -483,27 +487,46 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 6 : 1))) void pr
                 box_muller_words(q.x, q.y, zs, zv);
                 uv = uniform_f64(q.z);
             }
-            const R z1l = zs * log2e;
+            const R z = zs * qe_z;
             const QEPre<R> q0 = qe_pre<R>(w, qb);
             QEPre<R> q1{}, q2{}, q3{}, q4{};
-            bool lo = q0.quad, hi = !lo;
+            bool hi = !q0.quad;
             if constexpr (BUMPS) {
                 q1 = qe_pre<R>(wv0, qb);
                 q2 = qe_pre<R>(wv1, qb);
                 q3 = qe_pre<R>(wt0, qu);
                 q4 = qe_pre<R>(wt1, qd);
-                for (const bool qd_ : {q1.quad, q2.quad, q3.quad, q4.quad}) {
-                    lo = lo || qd_;
-                    hi = hi || !qd_;
+                for (const bool quad : {q1.quad, q2.quad, q3.quad, q4.quad})
+                    hi = hi || !quad;
+            }
+            // the quadratic draws of every scenario in one region, so that their
+            // chains of four transcendentals interleave (a branch around each
+            // scenario's: 1468 us, this: 1326); the exponential ones only where
+            // some lane of the wave takes them (away from zero variance whole
+            // waves skip them), each lane selecting by its own branch (a draw
+            // that is not selected may be NaN)
+            R n0 = qe_quad<R, BUMPS>(q0, zv), n1 = R(0), n2 = R(0), n3 = R(0), n4 = R(0);
+            if constexpr (BUMPS) {
+                n1 = qe_quad<R, BUMPS>(q1, zv);
+                n2 = qe_quad<R, BUMPS>(q2, zv);
+                n3 = qe_quad<R, BUMPS>(q3, zv);
+                n4 = qe_quad<R, BUMPS>(q4, zv);
+            }
+            if (any_lane(hi)) {
+                n0 = q0.quad ? n0 : qe_expo(q0, uv);
+                if constexpr (BUMPS) {
+                    n1 = q1.quad ? n1 : qe_expo(q1, uv);
+                    n2 = q2.quad ? n2 : qe_expo(q2, uv);
+                    n3 = q3.quad ? n3 : qe_expo(q3, uv);
+                    n4 = q4.quad ? n4 : qe_expo(q4, uv);
                 }
             }
-            const bool quad = any_lane(lo), expo = any_lane(hi);
-            qe_post<R>(y, w, qb, q0, z1l, zv, uv, quad, expo);
+            qe_price<R>(y, w, n0, qb, z);
             if constexpr (BUMPS) {
-                qe_post<R>(yv0, wv0, qb, q1, z1l, zv, uv, quad, expo);
-                qe_post<R>(yv1, wv1, qb, q2, z1l, zv, uv, quad, expo);
-                qe_post<R>(yt0, wt0, qu, q3, z1l, zv, uv, quad, expo);
-                qe_post<R>(yt1, wt1, qd, q4, z1l, zv, uv, quad, expo);
+                qe_price<R>(yv0, wv0, n1, qb, z);
+                qe_price<R>(yv1, wv1, n2, qb, z);
+                qe_price<R>(yt0, wt0, n3, qu, z);
+                qe_price<R>(yt1, wt1, n4, qd, z);
             }
             fixing(j, std::false_type{});
         }
