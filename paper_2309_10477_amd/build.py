@@ -39,9 +39,6 @@ FLAGS = [
 ]
 PER_FILE = {
     "price_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    # the adjoint and batched paths: 1% and 1.6% faster
-    "adjoint_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    "batch_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     # the exact sampler waits on its own chains (four waves per SIMD): 2% faster
     "exact_kernel.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }

@@ -12,6 +12,36 @@
 namespace heston {
 
 // ---------------------------------------------------------------------------
+// Single-precision transcendental instructions, each issued at raised wave
+// priority.  The path loops are bound by VALU issue: plain FP32 and logic
+// instructions of a SIMD's waves overlap and take 2.4 cycles each, a
+// transcendental takes 8.4 by itself, but in a loop of one transcendental and
+// five plain instructions (a Milstein step's mix) all six take 26.4 cycles, not
+// 8.4 + 5 x 2.4: waves arrive at transcendentals one after the other and the
+// plain instructions between find no partner.  Letting a wave that has reached
+// one issue it first brings the six to 19.8 cycles.  At 2^20 x 252: daily Asian
+// 611 -> 544 us, QE 1342 -> 1133; adjoint Asian 2^21 x 365 2222 -> 2000; a batch of
+// 64 options 5440 -> 4760.
+// The s_setprio behind the instruction is also the one wait state that a
+// transcendental's result needs before a plain instruction reads it.
+#define HESTON_TRANS_F32(name, op, src)                                                            \
+    __device__ __forceinline__ float name(float x)                                                 \
+    {                                                                                              \
+        float r;                                                                                   \
+        asm("s_setprio 1\n\t" op " %0, " src "%1\n\ts_setprio 0" : "=v"(r) : "v"(x));            \
+        return r;                                                                                  \
+    }
+HESTON_TRANS_F32(sqrt_f32, "v_sqrt_f32", "")
+HESTON_TRANS_F32(sqrt_neg_f32, "v_sqrt_f32", "-") // sqrt(-x)
+HESTON_TRANS_F32(rsq_f32, "v_rsq_f32", "")
+HESTON_TRANS_F32(rcp_f32, "v_rcp_f32", "")
+HESTON_TRANS_F32(log2_f32, "v_log_f32", "")
+HESTON_TRANS_F32(exp2_f32, "v_exp_f32", "")
+HESTON_TRANS_F32(cos_rev_f32, "v_cos_f32", "") // argument in revolutions
+HESTON_TRANS_F32(sin_rev_f32, "v_sin_f32", "")
+#undef HESTON_TRANS_F32
+
+// ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds; each round
 // multiplies counter words 0 and 2 by fixed 32-bit constants (full 64-bit
 // products), mixes the high halves with words 1, 3 and the key, and the key
@@ -63,9 +93,9 @@ __device__ __forceinline__ double uniform_f64(uint32_t w)
 __device__ __forceinline__ void box_muller(float ua, float ub, float &za, float &zb)
 {
     constexpr float M2LN2 = -1.38629436111989061883f; // -2 ln 2
-    const float rad = __builtin_amdgcn_sqrtf(M2LN2 * __builtin_amdgcn_logf(ua));
-    za = rad * __builtin_amdgcn_cosf(ub);
-    zb = rad * __builtin_amdgcn_sinf(ub);
+    const float rad = sqrt_f32(M2LN2 * log2_f32(ua));
+    za = rad * cos_rev_f32(ub);
+    zb = rad * sin_rev_f32(ub);
 }
 // The same pair divided by SQRT_2LN2 = sqrt(2 ln 2): sqrt(-log2 ua) (cos 2 pi ub,
 // sin 2 pi ub), for callers that fold the factor into the constants the
@@ -73,9 +103,9 @@ __device__ __forceinline__ void box_muller(float ua, float ub, float &za, float 
 constexpr double SQRT_2LN2 = 1.17741002251547469101;
 __device__ __forceinline__ void box_muller_log2(float ua, float ub, float &za, float &zb)
 {
-    const float rad = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(ua));
-    za = rad * __builtin_amdgcn_cosf(ub);
-    zb = rad * __builtin_amdgcn_sinf(ub);
+    const float rad = sqrt_neg_f32(log2_f32(ua));
+    za = rad * cos_rev_f32(ub);
+    zb = rad * sin_rev_f32(ub);
 }
 // Box-Muller pair of two random words, in double: the map above at the words'
 // uniforms, through the LDS tables (load_fp64_tables).
@@ -116,17 +146,17 @@ __device__ __forceinline__ void inv_normal_lower_bits2(uint32_t xa, uint32_t xb,
 {
     constexpr float LN2F = 0.69314718055994530942f;
     const float a0 = (float)(2u * xa + 1u) * 0x1p-30f, a1 = (float)(2u * xb + 1u) * 0x1p-30f; // 2u
-    const float l0 = __builtin_amdgcn_logf(a0 * (2.0f - a0)); // log2(4u(1-u)) <= 0
-    const float l1 = __builtin_amdgcn_logf(a1 * (2.0f - a1));
+    const float l0 = log2_f32(a0 * (2.0f - a0)); // log2(4u(1-u)) <= 0
+    const float l1 = log2_f32(a1 * (2.0f - a1));
     float q0 = horner(INV_NORMAL_CENTRAL, l0 * -LN2F - INV_NORMAL_CENTER);
     float q1 = horner(INV_NORMAL_CENTRAL, l1 * -LN2F - INV_NORMAL_CENTER);
     constexpr float SPLIT = -INV_NORMAL_W_SPLIT / LN2F;
     const bool t0 = l0 < SPLIT, t1 = l1 < SPLIT;
     if (t0 || t1) {
         const float p0 = horner(INV_NORMAL_TAIL,
-                                __builtin_amdgcn_sqrtf(l0 * -LN2F) - INV_NORMAL_TAIL_CENTER);
+                                sqrt_f32(l0 * -LN2F) - INV_NORMAL_TAIL_CENTER);
         const float p1 = horner(INV_NORMAL_TAIL,
-                                __builtin_amdgcn_sqrtf(l1 * -LN2F) - INV_NORMAL_TAIL_CENTER);
+                                sqrt_f32(l1 * -LN2F) - INV_NORMAL_TAIL_CENTER);
         q0 = t0 ? p0 : q0;
         q1 = t1 ? p1 : q1;
     }
@@ -137,13 +167,13 @@ __device__ __forceinline__ void inv_normal_lower_bits2(uint32_t xa, uint32_t xb,
 __device__ __forceinline__ double inv_normal_lower(double u) { return normcdfinv(u); }
 
 // Real-typed helpers.
-__device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ float fast_sqrt(float x) { return sqrt_f32(x); }
 __device__ __forceinline__ double fast_sqrt(double x) { return sqrt_nonneg(x); }
-__device__ __forceinline__ float fast_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ float fast_rsqrt(float x) { return rsq_f32(x); }
 __device__ __forceinline__ double fast_rsqrt(double x) { return rsqrt_pos(x); }
 __device__ __forceinline__ float fast_exp(float x)
 {
-    return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
+    return exp2_f32(x * 1.44269504088896340736f);
 }
 __device__ __forceinline__ double fast_exp(double x) { return exp_plain(x); }
 

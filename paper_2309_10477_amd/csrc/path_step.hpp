@@ -406,7 +406,7 @@ __device__ __forceinline__ void qe_draws(uint32_t j, uint32_t plo, uint32_t phi,
     }
 }
 
-__device__ __forceinline__ float qe_log(float x) { return __builtin_amdgcn_logf(x) * 0.69314718055994530942f; }
+__device__ __forceinline__ float qe_log(float x) { return log2_f32(x) * 0.69314718055994530942f; }
 __device__ __forceinline__ double qe_log(double x) { return log(x); }
 
 // b + Zv as a plain rounded sum, never contracted with the Box-Muller product

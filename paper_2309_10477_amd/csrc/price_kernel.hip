@@ -117,7 +117,7 @@ template <class R> __device__ __forceinline__ Grid<R> grid(const StepCoef &c, do
 // max(w, 0) as one v_med3 (no NaN canonicalisation of the loop-carried w).
 __device__ __forceinline__ float clamp0(float w) { return __builtin_amdgcn_fmed3f(w, 0.0f, 3.0e38f); }
 __device__ __forceinline__ double clamp0(double w) { return w > 0.0 ? w : 0.0; }
-__device__ __forceinline__ float exp2r(float y) { return __builtin_amdgcn_exp2f(y); }
+__device__ __forceinline__ float exp2r(float y) { return exp2_f32(y); }
 __device__ __forceinline__ double exp2r(double y) { return exp2_plain(y); }
 
 // One scaled step on grid g; z1l = Z1 / ln 2, a_g = kappa theta dt^2 +
@@ -203,9 +203,9 @@ template <class R> __device__ __forceinline__ QEGrid<R> qe_grid(const StepCoef &
     return g;
 }
 
-__device__ __forceinline__ float fast_log(float x) { return __builtin_amdgcn_logf(x) * (float)LN2; }
+__device__ __forceinline__ float fast_log(float x) { return log2_f32(x) * (float)LN2; }
 __device__ __forceinline__ double fast_log(double x) { return log(x); }
-__device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float fast_rcp(float x) { return rcp_f32(x); }
 __device__ __forceinline__ double fast_rcp(double x) { return rcp_pos(x); }
 
 // The variance step of one scenario, in parts; zv the normal of the quadratic
