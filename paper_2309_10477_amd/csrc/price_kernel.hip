@@ -273,9 +273,9 @@ __device__ __forceinline__ bool any_lane(bool c)
 }
 
 // Single-precision QE asks for four waves per SIMD or more: it is bound by issue
-// (five scenarios' 34 transcendentals and about 150 plain instructions a step),
-// and the bound only steers the schedule (1326 us at 2^20 x 252; asked for six
-// 1338, five 1332, nothing 1338).  The other variants keep the default.
+// (five scenarios' 34 transcendentals and about 130 plain instructions a step)
+// and the request steers the schedule: 1132 us at 2^20 x 252 asked for four or
+// six, 1217 not asked.  The other variants keep the default.
 // SPLIT (small FP64 launches with fused bumps, Milstein, Philox, European or
 // arithmetic Asian): each lane runs one scenario of one path -- lane l of a
 // wave takes path l / 5 of the wave's SPLIT_PATHS_PER_WAVE and scenario l % 5
@@ -501,7 +501,8 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 4 : 1))) void pr
             }
             // the quadratic draws of every scenario in one region, so that their
             // chains of four transcendentals interleave (a branch around each
-            // scenario's: 1468 us, this: 1326); the exponential ones only where
+            // scenario's: 1468 us, this: 1326, before the transcendentals'
+            // raised priority); the exponential ones only where
             // some lane of the wave takes them (away from zero variance whole
             // waves skip them), each lane selecting by its own branch (a draw
             // that is not selected may be NaN)
