@@ -58,7 +58,7 @@ FP32_VECTOR_PEAK = 157.3e12
 # a 256 MiB device copy reads under the same counters); see
 # profiles/price_kernel_asian_2p20x252_fp32_bumps_hbm_counters.md.  Set to None
 # whenever the kernel changes until the counters are taken again.
-TRAFFIC_BYTES_PER_LAUNCH = 838_265
+TRAFFIC_BYTES_PER_LAUNCH = 829_397
 # VALU utilisation of the path kernel from SQ counter passes of the same
 # build: the fraction of SIMD quad-cycles that issue a VALU instruction, the
 # share of lanes active in them, and the FLOP the hardware counted; see
