@@ -213,6 +213,17 @@ def test_fp32_all_types(hm, ctx, opt_type):
     check_records(d, PB, opt_type, N, seed, 0, n, 1, 0, None, True)
 
 
+@pytest.mark.parametrize("N", [1, 2, 3, 64])
+@pytest.mark.parametrize("opt_type", [oracle.ASIAN_PUT, oracle.GEO_ASIAN_CALL])
+@pytest.mark.parametrize("scheme", [0, 1])
+def test_fp32_every_step_fixing(hm, ctx, opt_type, N, scheme):
+    """The loop without fixing flags walks two steps at a time: no pair, pairs
+    only, and a pair and a half."""
+    opts = hm.Options(precision=hm.FP32, scheme=scheme)
+    d = dump(hm, ctx, PB, opt_type, 500, N, 7, 0, 500, opts)
+    check_records(d, PB, opt_type, N, 7, 0, 500, 1, scheme, None, True)
+
+
 @pytest.mark.parametrize("scheme", [3, 4, 5, 6])
 def test_euler_and_fixes_fp32(hm, ctx, scheme):
     n, N, seed = 4096 + 100, 63, 9
