@@ -58,17 +58,17 @@ FP32_VECTOR_PEAK = 157.3e12
 # a 256 MiB device copy reads under the same counters); see
 # profiles/price_kernel_asian_2p20x252_fp32_bumps_hbm_counters.md.  Set to None
 # whenever the kernel changes until the counters are taken again.
-TRAFFIC_BYTES_PER_LAUNCH = 829_397
+TRAFFIC_BYTES_PER_LAUNCH = 845_414
 # VALU utilisation of the path kernel from SQ counter passes of the same
 # build: the fraction of SIMD quad-cycles that issue a VALU instruction, the
 # share of lanes active in them, and the FLOP the hardware counted; see
 # profiles/valu_utilisation_counters.md.  Set to None whenever the kernel
 # changes until the counters are taken again.
 VALU_COUNTERS = {
-    "simd_valu_busy": 0.937,        # (SQ_ACTIVE_INST_VALU - SQ_ACTIVE_INST_VALU2) / SIMD quad-cycles
+    "simd_valu_busy": 0.932,        # (SQ_ACTIVE_INST_VALU - SQ_ACTIVE_INST_VALU2) / SIMD quad-cycles
     "valu_lane_util": 0.9994,       # SQ_THREAD_CYCLES_VALU / (SQ_ACTIVE_INST_VALU x 64)
-    "valu_utilisation": 0.937,      # their product: the path kernel's share of VALU issue capacity
-    "valubusy_amd_formula": 1.344,  # VALUBusy as rocprof defines it (counts dual-issued quad-cycles twice)
+    "valu_utilisation": 0.931,      # their product: the path kernel's share of VALU issue capacity
+    "valubusy_amd_formula": 1.341,  # VALUBusy as rocprof defines it (counts dual-issued quad-cycles twice)
     "counted_flop_per_path_step": 112.9,  # 64 x (SQ_INSTS_VALU_FLOPS_FP32 + _TRANS + FP64 + _TRANS) / path-steps
 }
 
