@@ -184,11 +184,11 @@ __device__ __forceinline__ Cx bessel_sum(Cx q, const double *rc, double nu, bool
         t = t * (q * f3);
         s = s + t;
     };
-    // k > |z| / 2 and |t| < 1e-17 |s|, compared squared
+    // k > |z| / 2 (as k^4 > |q|^2) and |t| < 1e-17 |s|, the moduli by their parts:
+    // S reaches e^600, whose square is beyond double's range
     auto settled = [&](int k) {
         const double k2 = (double)(k * k);
-        return k2 * k2 > q2 &&
-               t.re * t.re + t.im * t.im < 1e-34 * (s.re * s.re + s.im * s.im);
+        return k2 * k2 > q2 && fabs(t.re) + fabs(t.im) < 1e-17 * (fabs(s.re) + fabs(s.im));
     };
     for (int k = 0; k < RC_TABLE; k += 4) {
         four(rc[k], rc[k + 1], rc[k + 2], rc[k + 3]);
@@ -272,6 +272,14 @@ __device__ __forceinline__ Cx log_phi_part(const ExactLaunch &L, const PhiCtx &p
     return lp;
 }
 
+// ln |s|; scaled where the square of a part could leave double's range.
+__device__ __forceinline__ double log_modulus(Cx s)
+{
+    const bool big = fabs(s.re) + fabs(s.im) > 0x1p500;
+    const double f = big ? 0x1p-500 : 1.0, re = s.re * f, im = s.im * f;
+    return 0.5 * log_pos(re * re + im * im) + (big ? 500.0 * 0.69314718055994530942 : 0.0);
+}
+
 // Conditional mean and standard deviation of I from log Phi at a = h, 2h (even
 // and odd lanes).
 __device__ __forceinline__ void moments(const ExactLaunch &L, const PhiCtx &pc, const double *rc,
@@ -282,7 +290,7 @@ __device__ __forceinline__ void moments(const ExactLaunch &L, const PhiCtx &pc, 
     Cx s;
     double q2;
     const Cx lp = log_phi_part(L, pc, rc, (threadIdx.x & 1) ? 2.0 * h : h, &s, &q2, bad);
-    const Cx l{lp.re + 0.5 * log_pos(s.re * s.re + s.im * s.im), lp.im + angle_scaled(s.re, s.im)};
+    const Cx l{lp.re + log_modulus(s), lp.im + angle_scaled(s.re, s.im)};
     const double ore = row_move<0xB1>(l.re), oim = row_move<0xB1>(l.im);
     const bool odd = threadIdx.x & 1;
     const double re0 = odd ? ore : l.re, re1 = odd ? l.re : ore;

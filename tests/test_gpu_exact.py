@@ -99,6 +99,22 @@ def test_grid_and_group_edges(hm, ctx, change, opt, N, n):
     check(hm, ctx, PB.replace(**change), opt, N, 11, n)
 
 
+@pytest.mark.parametrize("change,N,n", [
+    (dict(T=.0738, v0=.02024, kappa=2.081, theta=.003698, sigma=.0526), 1, 40),
+    (dict(T=.709, v0=.0564, kappa=.1113, theta=.01472, sigma=.02748), 1, 40),
+    (dict(T=.184, v0=.0204, kappa=.1174, theta=.06406, sigma=.0287), 1, 40)],
+    ids=["360-400", "360-430", "590"])
+def test_bessel_series_near_the_end_of_its_range(hm, ctx, change, N, n):
+    """|z| of the Bessel argument between 355, where |S|^2 leaves double's
+    range, and the sampler's limit of 600."""
+    p = PB.replace(**change)
+    _, rec = check(hm, ctx, p, oracle.EURO_CALL, N, 11, n)
+    D = p.T / N
+    z = 4 * p.kappa * math.exp(-0.5 * p.kappa * D) / (p.sigma ** 2 * -math.expm1(-p.kappa * D)) \
+        * np.sqrt(p.v0 * rec[:, 1])
+    assert ((z > 355) & (z < 600)).mean() > 0.5
+
+
 def test_explicit_fixings_and_wide_indices(hm, ctx):
     check(hm, ctx, PB, oracle.ASIAN_PUT, 6, (9 << 40) | 5, 200, first=(1 << 32) + 11,
           fixings=(2, 3, 6))
