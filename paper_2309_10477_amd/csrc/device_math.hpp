@@ -175,7 +175,7 @@ __device__ __forceinline__ float fast_exp(float x)
 {
     return exp2_f32(x * 1.44269504088896340736f);
 }
-__device__ __forceinline__ double fast_exp(double x) { return exp_plain(x); }
+__device__ __forceinline__ double fast_exp(double x) { return exp_low(x); }
 
 template <class R> __device__ __forceinline__ R to_real(double v) { return (R)v; }
 

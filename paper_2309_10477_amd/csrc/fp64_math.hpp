@@ -152,7 +152,8 @@ __device__ __forceinline__ double exp2_plain(double y)
 }
 
 // e^x: x = n ln 2 + f with ln 2 in two parts, e^f = 1 + f q(f), q of degree 10
-// (near-minimax over |f| <= ln 2 / 2, 1.8e-17).
+// (near-minimax over |f| <= ln 2 / 2, 1.8e-17).  For |x| up to 1e40: f is of the
+// order of x's last place there, and its eleventh power overflows beyond.
 __device__ __forceinline__ double exp_plain(double x)
 {
     const double n = rint(x * 0x1.71547652b82fep+0);
@@ -170,6 +171,11 @@ __device__ __forceinline__ double exp_plain(double x)
     q = fma(f, q, 1.0);
     return __builtin_amdgcn_ldexp(fma(f, q, 1.0), (int)n);
 }
+
+// e^x for any x below 1e40, 0 far below: x is cut off where e^x is 0 (a path's
+// log-price falls below -1e40 with an initial variance of that order).  NaN stays.
+// The cut takes 2% of the FP64 Asian adjoint's forward pass.
+__device__ __forceinline__ double exp_low(double x) { return exp_plain(x < -1100.0 ? -1100.0 : x); }
 
 // ln(x) of a normal x > 0.
 __device__ __forceinline__ double log_pos(double x) { return -0.5 * neg2_log(x, 0); }

@@ -117,7 +117,7 @@ __device__ Cx log_transform(const GeoControl &g, Cx u, GeoShared &sh)
             const Cx rm = (-c1 - d) * h, rp = (d - c1) * h;
             double ec, es;
             cos_sin(-tau * d.im, ec, es);
-            const double em = exp_plain(-tau * d.re);
+            const double em = exp_low(-tau * d.re);
             const Cx e{em * ec, em * es};
             const Cx diff = rm - rp;
             const double n2 = rcp_pos(diff.re * diff.re + diff.im * diff.im);

@@ -108,6 +108,27 @@ def test_adjoint_fixing_flags_of_a_segment(hm, ctx, N, every, fix, scheme):
     check_against_tangent(d, PB, 2, N, 3, 0, 300, 0, scheme, fix)
 
 
+@pytest.mark.parametrize("scheme", [0, 1])
+@pytest.mark.parametrize("opt_type", [1, 3])
+def test_fp64_vanishing_price_under_an_enormous_variance(hm, ctx, opt_type, scheme):
+    """v0 = 1e50: e^x is 0 at every date, a put pays K, and only r moves its
+    price, in the adjoint's two passes and in a batch."""
+    p = PB.replace(v0=1e50)
+    price, grads, d = adjoint_per_path(hm, ctx, p, opt_type, 300, 8, 3, 0, 8, scheme)
+    pay = p.K * math.exp(-p.r * p.T)
+    want = [0.0, 0.0, -p.T * pay, 0.0, 0.0, 0.0, 0.0]
+    assert price[0] == pytest.approx(pay, rel=1e-14)
+    assert [g[0] for g in grads] == pytest.approx(want, rel=1e-14)
+    assert d[:, 0] == pytest.approx(pay, rel=1e-14)
+    rq = [dict(params=p.__dict__, type=opt_type, n_steps=8, n_paths=300, seed=3, want=w)
+          for w in (hm.WANT_PATHWISE, hm.WANT_ADJOINT)]
+    res, _ = ctx.price_batch(rq, hm.Options(scheme=scheme, greeks=hm.GREEKS_PATHWISE))
+    for r in res:
+        assert r["price"][0] == pytest.approx(pay, rel=1e-14)
+        assert r["pw_rho"][0] == pytest.approx(want[2], rel=1e-14)
+    assert [a[0] for a in res[1]["adj"]] == pytest.approx(want, rel=1e-14)
+
+
 @pytest.mark.parametrize("every", [8, 16])
 @pytest.mark.parametrize("opt_type", [0, 2])
 def test_adjoint_fp32_matches_tangent(hm, ctx, every, opt_type):
