@@ -1030,7 +1030,8 @@ static heston_status run_exact(heston_ctx *c, const Request &q, uint64_t first, 
     E.n_groups = (uint32_t)(((count + rounds - 1) / rounds + per_block - 1) / per_block * per_block);
     heston_status st;
     if ((st = upload_fix_bits(c, q, &E.fix_bits)) != HESTON_OK ||
-        (st = reserve(c, c->exact_scratch, (size_t)EXACT_MAX_GRID * E.n_groups * 8)) != HESTON_OK ||
+        (st = reserve(c, c->exact_scratch,
+                      ((size_t)EXACT_FAR_POINTS * E.n_groups + EXACT_LDS_POINTS) * 8)) != HESTON_OK ||
         (st = reserve(c, c->partials, (size_t)(E.n_groups / per_block) * EXACT_REC * 8)) != HESTON_OK ||
         (st = reserve(c, c->rep_sums, EXACT_REC * 8)) != HESTON_OK)
         return st;

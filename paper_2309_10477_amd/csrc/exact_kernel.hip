@@ -466,7 +466,7 @@ __global__ __launch_bounds__(BLOCK, 4) void exact_kernel(const ExactLaunch L)
     const double D = L.D;
     if (group < L.n_groups) {
         double *row = sh.w[threadIdx.x / GROUP];
-        double *far = L.scratch + (uint64_t)group * EXACT_MAX_GRID;
+        double *far = L.scratch + (uint64_t)group * EXACT_FAR_POINTS;
         for (uint64_t i = group; i < L.n_paths; i += L.n_groups) {
             const uint64_t p = L.first_path + i;
             Draw dr{(uint32_t)p, (uint32_t)(p >> 32), 0u, (uint32_t)L.seed,

@@ -127,6 +127,12 @@ constexpr double EXACT_MAX_POISSON_MEAN = 700.0;
 constexpr uint32_t EXACT_MAX_GRID = 16384;      // characteristic-function points per draw
 constexpr int EXACT_GROUP = 16;                 // lanes of a path
 constexpr uint32_t EXACT_LDS_POINTS = 208;      // points a group keeps in LDS
+// ... and in its scratch row: the points beyond those in LDS, whose bytes pay
+// for the partials of sixteen times as many blocks as with a path per lane, so
+// that a call needs no more of the context's budget than it did then.  Row l's
+// point i (counted over the whole grid) is at l EXACT_FAR_POINTS + i, so the
+// rows end EXACT_LDS_POINTS later.
+constexpr uint32_t EXACT_FAR_POINTS = EXACT_MAX_GRID - EXACT_LDS_POINTS;
 constexpr uint32_t EXACT_MAX_GROUPS = 16384;    // resident groups: four blocks of 16 on 256 CUs
 constexpr int EXACT_REC = N_ACC + 2;            // partial record: estimator sums, failures, pad
 struct ExactLaunch {
@@ -147,7 +153,7 @@ struct ExactLaunch {
     uint64_t seed;
     uint64_t first_path, n_paths;
     uint32_t n_groups;        // groups of the launch; group l takes paths l, l + n_groups, ...
-    double *scratch;          // device [n_groups][EXACT_MAX_GRID]: Re Phi / j on the grid
+    double *scratch;          // device, n_groups EXACT_FAR_POINTS + EXACT_LDS_POINTS: Re Phi / j
     double *partials;         // device [blocks][EXACT_REC]
     double *dump;             // device [n_paths][DUMP_WIDTH] or null
 };
