@@ -931,7 +931,7 @@ static heston_status geo_control_setup(heston_ctx *c, const Request &q, GeoContr
     std::memcpy(g.gl_x, rule.x, sizeof(g.gl_x));
     std::memcpy(g.gl_w, rule.w, sizeof(g.gl_w));
     if ((st = reserve(c, c->geo_buf, GEO_BUF_DOUBLES * 8)) != HESTON_OK ||
-        (st = reserve(c, c->geo_partials, (size_t)geo_node_blocks() * 8)) != HESTON_OK)
+        (st = reserve(c, c->geo_partials, (size_t)GEO_NODE_BLOCKS * 8)) != HESTON_OK)
         return st;
     if (!c->host_geo_dev) {
         if (!c->host_geo)

@@ -18,9 +18,9 @@
 //
 // A gap's step is linear-fractional in B, so with B = x / y it is a 2x2 matrix
 // on (x, y), N = M / (r_- - r_+), whose entries depend on a and tau alone; N is
-// scaled so that the logarithm's argument is y' / y.  A block takes
-// GEO_SLOTS transforms, 32 threads each, and goes through the gaps
-// GEO_CHUNK at a time: all threads form the matrices (square roots,
+// scaled so that the logarithm's argument is y' / y.  A block takes eight
+// transforms (32 in long ranges), its threads shared evenly, and goes through the
+// gaps 64 (16) at a time: all threads form the matrices (square roots,
 // exponentials, divisions), one thread per transform multiplies the vectors
 // through them, and all threads take the arguments of y' / y (the moduli
 // telescope).  One thread per transform doing all of it in order was a chain of
@@ -53,14 +53,12 @@ constexpr int GEO_MAX_LOG2_RANGE = 14; // v_max <= 2^14
 // width 8 on the tested parameter sets).
 constexpr uint32_t GEO_PANEL_WIDTH = 4;
 static_assert(GEO_MAX_LOG2_RANGE < GEO_BOUND_POINTS, "bound table too short");
-constexpr uint32_t GEO_SLOTS = 8;              // transforms per block
-constexpr uint32_t GEO_LANES = BLOCK / GEO_SLOTS; // threads per transform
-constexpr uint32_t GEO_CHUNK = 64;             // gaps per round
-constexpr uint32_t GEO_RESCALE = 8;            // steps between rescalings of (x, y), unrolled
+// Transforms per block, whose threads they share evenly.
+constexpr uint32_t GEO_SLOTS = 8, GEO_SLOTS_MANY = 32;
+constexpr uint32_t GEO_SHORT_RANGE = 1024; // up to it GEO_SLOTS: see many_slots
 constexpr uint32_t GEO_MAX_NODES = 2u * (16u << GEO_MAX_LOG2_RANGE) / GEO_PANEL_WIDTH; // x 2 transforms
-constexpr uint32_t GEO_NODE_BLOCKS = GEO_MAX_NODES / GEO_SLOTS + 1; // and the two bounds and E[G]
-static_assert(GEO_CHUNK % GEO_RESCALE == 0, "whole groups of steps");
-static_assert(GEO_LANES == 32, "a transform's threads are half a wave");
+constexpr uint32_t GEO_CELLS = 512;            // gaps per round of a block, over its transforms
+constexpr uint32_t GEO_RESCALE = 8;            // steps between rescalings of (x, y), unrolled
 constexpr double GEO_TOL = 1e-15;
 
 __device__ __forceinline__ double fix_time(const GeoControl &g, uint32_t i)
@@ -68,12 +66,15 @@ __device__ __forceinline__ double fix_time(const GeoControl &g, uint32_t i)
     return (g.steps ? (double)g.steps[i] : (double)(i + 1)) * g.dt;
 }
 
-struct GeoShared {
-    Cx n[GEO_SLOTS][GEO_CHUNK][4];      // N of each gap: (11, 12, 21, 22)
-    Cx y[GEO_SLOTS][GEO_CHUNK + 1];     // y before the chunk and after each of its gaps
-    Cx end[GEO_SLOTS];                  // x / y and, in `log_y`, ln |y| of the last gap
-    double log_y[GEO_SLOTS];
-    double red[GEO_SLOTS];
+template <uint32_t SLOTS> struct GeoShared {
+    static constexpr uint32_t LANES = BLOCK / SLOTS, CHUNK = GEO_CELLS / SLOTS;
+    static_assert(CHUNK % GEO_RESCALE == 0 && LANES >= GEO_RESCALE, "whole groups of steps");
+    static_assert(LANES <= 32 && (LANES & (LANES - 1)) == 0, "a transform's threads within half a wave");
+    Cx n[SLOTS][CHUNK][4];              // N of each gap: (11, 12, 21, 22)
+    Cx y[SLOTS][CHUNK + 1];             // y before the chunk and after each of its gaps
+    Cx end[SLOTS];                      // x / y and, in `log_y`, ln |y| of the last gap
+    double log_y[SLOTS];
+    double red[SLOTS];
 };
 
 // Principal square root (non-negative real part) of z away from the ends of
@@ -86,28 +87,30 @@ __device__ __forceinline__ Cx lean_csqrt(Cx z)
     return z.re >= 0.0 ? Cx{t, o} : Cx{fabs(o), copysign(t, z.im)};
 }
 
-__device__ __forceinline__ double half_wave_sum(double v)
+// Sum over a transform's threads.
+template <uint32_t LANES> __device__ __forceinline__ double slot_sum(double v)
 {
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1)
-        v += __shfl_xor(v, off, 32);
+    for (uint32_t off = LANES / 2; off > 0; off >>= 1)
+        v += __shfl_xor(v, off, LANES);
     return v;
 }
 
 // Exponent of E[exp(u ln G)]: u ln S0 + A + B v0, for the transform of the
 // thread's slot; every thread of the block calls it.
-__device__ Cx log_transform(const GeoControl &g, Cx u, GeoShared &sh)
+template <uint32_t SLOTS> __device__ Cx log_transform(const GeoControl &g, Cx u, GeoShared<SLOTS> &sh)
 {
-    const uint32_t slot = threadIdx.x / GEO_LANES, lane = threadIdx.x % GEO_LANES;
+    constexpr uint32_t LANES = GeoShared<SLOTS>::LANES, CHUNK = GeoShared<SLOTS>::CHUNK;
+    const uint32_t slot = threadIdx.x / LANES, lane = threadIdx.x % LANES;
     const Cx w = u * (1.0 / (double)g.n_fix);
     const double c2 = 0.5 * g.sigma * g.sigma, h = 0.5 / c2;
     const Cx one{1.0, 0.0};
     double ar = 0.0, ai = 0.0, turn = 0.0; // this thread's share of A without the logarithms, of arg y
-    Cx x{0.0, 0.0}, y = one;               // threads 0 .. GEO_SLOTS - 1: slot threadIdx.x
+    Cx x{0.0, 0.0}, y = one;               // threads 0 .. SLOTS - 1: slot threadIdx.x
     double scale = 0.0;                    // powers of two taken out of (x, y)
-    for (uint32_t base = 0; base < g.n_fix; base += GEO_CHUNK) {
-        const uint32_t len = min(GEO_CHUNK, g.n_fix - base);
-        for (uint32_t i = lane; i < len; i += GEO_LANES) {
+    for (uint32_t base = 0; base < g.n_fix; base += CHUNK) {
+        const uint32_t len = min(CHUNK, g.n_fix - base);
+        for (uint32_t i = lane; i < len; i += LANES) {
             const uint32_t k = g.n_fix - 1 - (base + i); // from the last date to the first
             const double tau = fix_time(g, k) - (k ? fix_time(g, k - 1) : 0.0);
             const Cx a = w * (double)(g.n_fix - k);
@@ -135,7 +138,7 @@ __device__ Cx log_transform(const GeoControl &g, Cx u, GeoShared &sh)
             sh.n[slot][len + lane][1] = sh.n[slot][len + lane][2] = Cx{0.0, 0.0};
         }
         __syncthreads();
-        if (threadIdx.x < GEO_SLOTS) {
+        if (threadIdx.x < SLOTS) {
             const Cx(*n)[4] = sh.n[threadIdx.x];
             sh.y[threadIdx.x][0] = y;
             for (uint32_t i = 0; i < len; i += GEO_RESCALE) {
@@ -157,14 +160,14 @@ __device__ Cx log_transform(const GeoControl &g, Cx u, GeoShared &sh)
             }
         }
         __syncthreads();
-        for (uint32_t i = lane; i < len; i += GEO_LANES) {
+        for (uint32_t i = lane; i < len; i += LANES) {
             const Cx p = sh.y[slot][i], q = sh.y[slot][i + 1];
             turn += angle_scaled(q.re * p.re + q.im * p.im, q.im * p.re - q.re * p.im);
         }
         __syncthreads(); // the chunk is read before the next one overwrites it
     }
     const double f = g.kappa * g.theta / c2;
-    const Cx A{half_wave_sum(ar) - f * sh.log_y[slot], half_wave_sum(ai) - f * half_wave_sum(turn)};
+    const Cx A{slot_sum<LANES>(ar) - f * sh.log_y[slot], slot_sum<LANES>(ai) - f * slot_sum<LANES>(turn)};
     return u * g.lnS0 + A + sh.end[slot] * g.v0;
 }
 
@@ -184,24 +187,25 @@ __device__ double bound_part(const GeoControl &g, Cx lt, double v, int which)
 }
 
 // Slot numbers 2 k + which: the bounds at v = 2^k; then E[G].
+template <uint32_t SLOTS>
 __global__ __launch_bounds__(BLOCK) void geo_bound_kernel(const GeoControl g, double *bound,
                                                           double *out)
 {
-    __shared__ GeoShared sh;
+    __shared__ GeoShared<SLOTS> sh;
+    constexpr uint32_t LANES = GeoShared<SLOTS>::LANES;
     load_fp64_tables<BLOCK>();
-    const uint32_t t = blockIdx.x * GEO_SLOTS + threadIdx.x / GEO_LANES;
+    const uint32_t t = blockIdx.x * SLOTS + threadIdx.x / LANES;
     const bool is_bound = t < 2 * GEO_BOUND_POINTS;
     const double v = is_bound ? ldexp(1.0, (int)(t >> 1)) : 0.0;
     const int which = is_bound ? (int)(t & 1) : 0;
-    const Cx lt = log_transform(g, Cx{which ? 0.0 : 1.0, v}, sh);
-    if (threadIdx.x % GEO_LANES != 0)
+    const Cx lt = log_transform<SLOTS>(g, Cx{which ? 0.0 : 1.0, v}, sh);
+    if (threadIdx.x % LANES != 0)
         return;
     if (is_bound)
         bound[t] = bound_part(g, lt, v, which);
     else if (t == 2 * GEO_BOUND_POINTS)
         out[2] = exp(lt.re); // E[G]
 }
-constexpr uint32_t GEO_BOUND_BLOCKS = 2 * GEO_BOUND_POINTS / GEO_SLOTS + 1;
 
 // Range of the integral: the first 2^k (k <= GEO_MAX_LOG2_RANGE) whose bound
 // is below tolerance, or 0 if none is.
@@ -215,21 +219,25 @@ __device__ uint32_t range_from(const double *bound, double EG, double K)
 }
 
 // Gauss-Legendre nodes of the integral over [0, range], two transforms per
-// node.  With a `fixed` range the three slots after the nodes evaluate the
-// modulus bound at v = fixed (out[4], out[5]) and E[G] (out[2]); otherwise the
-// range comes from the bound table of geo_bound_kernel.
+// node, from block `block0` of the whole range on; a later launch (block0 > 0)
+// adds to the partials of the one before.  With a `fixed` range the three slots
+// after the nodes evaluate the modulus bound at v = fixed (out[4], out[5]) and
+// E[G] (out[2]); otherwise the range comes from the bound table of
+// geo_bound_kernel.
+template <uint32_t SLOTS>
 __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uint32_t fixed,
-                                                         const double *bound, double *out,
-                                                         double *partials)
+                                                         uint32_t block0, const double *bound,
+                                                         double *out, double *partials)
 {
-    __shared__ GeoShared sh;
+    __shared__ GeoShared<SLOTS> sh;
+    constexpr uint32_t LANES = GeoShared<SLOTS>::LANES;
     const uint32_t range = fixed ? fixed : range_from(bound, out[2], g.K);
     const uint32_t width = range < GEO_PANEL_WIDTH ? range : GEO_PANEL_WIDTH;
     const uint32_t panels = width ? range / width : 0u;
-    const uint32_t t = blockIdx.x * GEO_SLOTS + threadIdx.x / GEO_LANES;
+    const uint32_t first = (block0 + blockIdx.x) * SLOTS, t = first + threadIdx.x / LANES;
     const uint32_t n_nodes = 32u * panels;
-    if (blockIdx.x * GEO_SLOTS >= n_nodes + (fixed ? 3u : 0u)) { // nothing for the whole block
-        if (threadIdx.x == 0)
+    if (first >= n_nodes + (fixed ? 3u : 0u)) { // nothing for the whole block
+        if (threadIdx.x == 0 && block0 == 0)
             partials[blockIdx.x] = 0.0;
         return;
     }
@@ -246,9 +254,9 @@ __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uin
     } else if (is_bound) {
         v = (double)fixed;
     }
-    const Cx lt = log_transform(g, Cx{which ? 0.0 : 1.0, v}, sh);
-    if (threadIdx.x % GEO_LANES == 0) {
-        sh.red[threadIdx.x / GEO_LANES] = is_node ? weight * integrand_part(g, lt, v, which) : 0.0;
+    const Cx lt = log_transform<SLOTS>(g, Cx{which ? 0.0 : 1.0, v}, sh);
+    if (threadIdx.x % LANES == 0) {
+        sh.red[threadIdx.x / LANES] = is_node ? weight * integrand_part(g, lt, v, which) : 0.0;
         if (fixed && is_bound)
             out[4 + which] = bound_part(g, lt, v, which);
         else if (fixed && t == n_nodes + 2)
@@ -258,9 +266,9 @@ __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uin
     if (threadIdx.x == 0) {
         double b = 0.0;
 #pragma unroll
-        for (uint32_t k = 0; k < GEO_SLOTS; ++k)
+        for (uint32_t k = 0; k < SLOTS; ++k)
             b += sh.red[k];
-        partials[blockIdx.x] = b;
+        partials[blockIdx.x] = block0 ? partials[blockIdx.x] + b : b;
     }
 }
 
@@ -295,23 +303,34 @@ __global__ __launch_bounds__(BLOCK) void geo_finish_kernel(const GeoControl g, u
 
 } // namespace
 
-uint32_t geo_node_blocks() { return GEO_NODE_BLOCKS; }
-
+// A range up to 1024 takes eight transforms per block: its blocks do not fill the
+// device, and more threads per transform shorten each (252 dates, range 1024: 121
+// us a call of 2000 paths, with 32 per block 138).  Beyond it the blocks queue, and
+// 32 per block run the serial chains of four times as many transforms in the same
+// instructions (range 2048: 191 -> 179 us, 246 -> 186 beside 2^18 paths; 4096: 337 ->
+// 287; twelve dates, searched range: 173 -> 109).
+static bool many_slots(const GeoControl &g) { return g.v_max > GEO_SHORT_RANGE; }
 static uint32_t fixed_blocks(const GeoControl &g)
 {
-    return (32u * (g.v_max / GEO_PANEL_WIDTH) + 3u + GEO_SLOTS - 1) / GEO_SLOTS;
+    const uint32_t slots = many_slots(g) ? GEO_SLOTS_MANY : GEO_SLOTS;
+    return (32u * (g.v_max / GEO_PANEL_WIDTH) + 3u + slots - 1) / slots;
 }
+static_assert(32u * GEO_SHORT_RANGE / GEO_PANEL_WIDTH / GEO_SLOTS < GEO_NODE_BLOCKS &&
+                  32u * GEO_MAX_FIXED_RANGE / GEO_PANEL_WIDTH / GEO_SLOTS_MANY < GEO_NODE_BLOCKS,
+              "fixed ranges within the partials buffer");
 
 hipError_t launch_geo_nodes_fixed(const GeoControl &g, double *partials, double *buf,
                                   hipStream_t stream)
 {
-    static_assert((32u * (GEO_MAX_FIXED_RANGE / GEO_PANEL_WIDTH) + 3u + GEO_SLOTS - 1) / GEO_SLOTS <=
-                      GEO_NODE_BLOCKS,
-                  "fixed range within the partials buffer");
     if (g.v_max < GEO_PANEL_WIDTH || g.v_max > GEO_MAX_FIXED_RANGE || g.v_max % GEO_PANEL_WIDTH)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(geo_node_kernel, dim3(fixed_blocks(g)), dim3(BLOCK), 0, stream, g, g.v_max,
-                       (const double *)buf, buf + GEO_OUT, partials);
+    const dim3 grid(fixed_blocks(g));
+    if (many_slots(g))
+        hipLaunchKernelGGL(geo_node_kernel<GEO_SLOTS_MANY>, grid, dim3(BLOCK), 0, stream, g, g.v_max,
+                           0u, (const double *)buf, buf + GEO_OUT, partials);
+    else
+        hipLaunchKernelGGL(geo_node_kernel<GEO_SLOTS>, grid, dim3(BLOCK), 0, stream, g, g.v_max, 0u,
+                           (const double *)buf, buf + GEO_OUT, partials);
     return hipGetLastError();
 }
 
@@ -327,13 +346,15 @@ hipError_t launch_geo_finish_fixed(const GeoControl &g, double *partials, double
 hipError_t launch_geo_price_search(const GeoControl &g, double *partials, double *buf,
                                    double *prices, hipStream_t stream)
 {
-    hipLaunchKernelGGL(geo_bound_kernel, dim3(GEO_BOUND_BLOCKS), dim3(BLOCK), 0, stream, g, buf,
-                       buf + GEO_OUT);
-    hipLaunchKernelGGL(geo_node_kernel, dim3(GEO_NODE_BLOCKS), dim3(BLOCK), 0, stream, g, 0u,
-                       (const double *)buf, buf + GEO_OUT, partials);
-    hipLaunchKernelGGL(geo_finish_kernel, dim3(1), dim3(BLOCK), 0, stream, g, 0u,
-                       GEO_NODE_BLOCKS, (const double *)buf, (const double *)partials,
-                       buf + GEO_OUT, prices);
+    constexpr uint32_t SLOTS = GEO_SLOTS_MANY;
+    hipLaunchKernelGGL(geo_bound_kernel<SLOTS>, dim3(2 * GEO_BOUND_POINTS / SLOTS + 1), dim3(BLOCK),
+                       0, stream, g, buf, buf + GEO_OUT);
+    // (all but the first launch exit at once up to a range of 8192)
+    for (uint32_t b = 0; b < GEO_MAX_NODES / SLOTS; b += GEO_NODE_BLOCKS)
+        hipLaunchKernelGGL(geo_node_kernel<SLOTS>, dim3(GEO_NODE_BLOCKS), dim3(BLOCK), 0, stream, g,
+                           0u, b, (const double *)buf, buf + GEO_OUT, partials);
+    hipLaunchKernelGGL(geo_finish_kernel, dim3(1), dim3(BLOCK), 0, stream, g, 0u, GEO_NODE_BLOCKS,
+                       (const double *)buf, (const double *)partials, buf + GEO_OUT, prices);
     return hipGetLastError();
 }
 

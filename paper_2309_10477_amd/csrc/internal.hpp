@@ -273,13 +273,15 @@ hipError_t launch_reduce(const PriceLaunch &L, double *rep_sums, hipStream_t str
 // discounted call and put prices of G, E[G], the Gil-Pelaez integral and the
 // two bounds at the end of the fixed range.  The prices are NaN when the
 // transform has not decayed by the end of the range (fixed: g.v_max, at most
-// GEO_MAX_FIXED_RANGE; search: 2^14).  `partials` (device [geo_node_blocks()])
+// GEO_MAX_FIXED_RANGE; search: 2^14).  `partials` (device [GEO_NODE_BLOCKS])
 // holds one double per block of the node kernel.
 constexpr int GEO_BOUND_POINTS = 15;
 constexpr int GEO_OUT = 2 * GEO_BOUND_POINTS;
 constexpr int GEO_BUF_DOUBLES = GEO_OUT + 6;
 constexpr uint32_t GEO_MAX_FIXED_RANGE = 4096;
-uint32_t geo_node_blocks();
+// Most blocks of a launch of the node kernel: a partial each, 16 KiB of the
+// context's budget.
+constexpr uint32_t GEO_NODE_BLOCKS = 2048;
 // The fixed range in two launches, so that the caller can start other work
 // between them; the call and put price go to `prices` (device-visible).
 hipError_t launch_geo_nodes_fixed(const GeoControl &g, double *partials, double *buf,

@@ -38,7 +38,6 @@ hipError_t launch_adjoint(const PriceLaunch &, double, double *, hipStream_t s)
     return fake::work(s);
 }
 hipError_t launch_exact(const ExactLaunch &, hipStream_t s) { return fake::work(s); }
-uint32_t geo_node_blocks() { return 2048; }
 hipError_t launch_geo_nodes_fixed(const GeoControl &, double *, double *, hipStream_t s)
 {
     return fake::work(s);
@@ -90,9 +89,30 @@ static void exact_budget()
     }
 }
 
+// The control's buffers take no more of the budget than with one partial per 256
+// transforms: four pages for the partials and one for the rest, at every range.
+static void control_budget()
+{
+    heston_opts o;
+    heston_default_opts(&o);
+    o.control_variate = HESTON_CONTROL_GEOMETRIC;
+    for (double T : {1.0, 0.01, 1e-4}) {
+        heston_params p = P;
+        p.T = T;
+        o.bump_T_abs = T / 100;
+        heston_ctx *c = nullptr;
+        CHECK(heston_ctx_create(0, nullptr, 0, &c) == HESTON_OK);
+        heston_result r;
+        CHECK(heston_price_greeks_ex(c, &p, HESTON_ASIAN_CALL, 10000, 12, 1, &o, &r) == HESTON_OK);
+        CHECK(c->geo_partials.bytes <= 4 * 4096 && c->geo_buf.bytes <= 4096);
+        CHECK(heston_ctx_destroy(c) == HESTON_OK);
+    }
+}
+
 int main()
 {
     exact_budget();
+    control_budget();
     for (auto &f : fake::faults) {
         printf("%s\n", f.c_str());
         failed = 1;

@@ -190,6 +190,20 @@ def test_control_mean_at_the_edges_of_its_chunks(hm, ctx, N):
                                          rel=1e-9)
 
 
+@pytest.mark.parametrize("N", [8, 16, 17, 48])
+@pytest.mark.parametrize("p", [PB, PB.replace(T=0.01, v0=0.01, theta=0.01, sigma=0.1),
+                               PB.replace(v0=0.01, theta=0.01, sigma=2.0, kappa=1.0)],
+                         ids=["short-range", "long-range", "search"])
+def test_control_mean_at_the_edges_of_its_layouts(hm, ctx, p, N):
+    """Eight transforms per block in a short range, 32 in a long (4096) and in a
+    searched one, whose dates go sixteen to a chunk: up to one chunk, more."""
+    opts = hm.Options(precision=1, control_variate=hm.CONTROL_GEOMETRIC,
+                      greeks=hm.GREEKS_PATHWISE)
+    for opt in (oracle.ASIAN_CALL, oracle.ASIAN_PUT):
+        r = ctx.price_greeks(p.__dict__, opt, 256, N, 3, opts)
+        assert r["cv_mean"] == pytest.approx(oracle.geometric_control_mean(p, opt, N, None), rel=1e-9)
+
+
 def test_full_size_variance_reduction_and_agreement(hm, ctx):
     """2^20 paths x 252 daily fixings, FP32: the control cuts the standard
     error at least fivefold and the two estimates agree within their errors."""
