@@ -826,6 +826,8 @@ heston_status heston_ctx_destroy(heston_ctx *c)
         return fail(HESTON_INVALID_ARGUMENT, "ctx is NULL");
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
+    if (c->side)
+        (void)hipStreamSynchronize(c->side);
     for (DevBuf *b : {&c->partials, &c->rep_sums, &c->fix_bits, &c->sobol_dirs, &c->sobol_shift, &c->sobol_hi, &c->sobol_perm, &c->sobol_low,
                       &c->bridge_start, &c->bridge_ops, &c->pay, &c->bump_partials,
                       &c->geo_buf, &c->geo_partials, &c->geo_steps, &c->exact_scratch,
@@ -840,10 +842,8 @@ heston_status heston_ctx_destroy(heston_ctx *c)
         (void)hipHostFree(c->host_geo);
     (void)hipEventDestroy(c->ev0);
     (void)hipEventDestroy(c->ev1);
-    if (c->side) {
-        (void)hipStreamSynchronize(c->side);
+    if (c->side)
         (void)hipStreamDestroy(c->side);
-    }
     delete c;
     return HESTON_OK;
 }
@@ -1051,6 +1051,17 @@ static heston_status run_exact(heston_ctx *c, const Request &q, uint64_t first, 
     return HESTON_OK;
 }
 
+// Waits for the side stream when a control call leaves early: an upload there
+// reads the caller's fixing dates, and the last kernel writes pinned host memory.
+struct SideDrain {
+    heston_ctx *c;
+    ~SideDrain()
+    {
+        if (c && c->side)
+            (void)hipStreamSynchronize(c->side);
+    }
+};
+
 static heston_status price_greeks_impl(heston_ctx *c, const heston_params *params,
                                        heston_option_type type, uint64_t n_paths,
                                        uint32_t n_steps, uint64_t seed, const heston_opts *opts,
@@ -1117,6 +1128,7 @@ static heston_status price_greeks_impl(heston_ctx *c, const heston_params *param
         return st;
     L.dump = nullptr;
     GeoControl gc;
+    SideDrain drain{L.cv ? c : nullptr};
     if (L.cv) {
         // the control's price (latency-bound, few waves) runs on the side
         // stream while the path kernel fills the device.  Its inputs are the
@@ -1150,6 +1162,7 @@ static heston_status price_greeks_impl(heston_ctx *c, const heston_params *param
                                         (double *)c->geo_buf.ptr, c->host_geo_dev, c->side));
         HIP_TRY(hipStreamSynchronize(c->side));
     }
+    drain.c = nullptr;
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, c->ev0, c->ev1));
 

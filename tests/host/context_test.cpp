@@ -109,8 +109,35 @@ static void control_budget()
     }
 }
 
+// Whichever call fails, a control request returns with its side stream idle --
+// its uploads read the caller's fixing dates, its last kernel writes pinned host
+// memory -- and the context frees nothing while a stream has work.
+static void control_error_returns()
+{
+    const uint32_t steps[] = {3, 6, 12};
+    heston_opts o;
+    heston_default_opts(&o);
+    o.control_variate = HESTON_CONTROL_GEOMETRIC;
+    o.fixing_steps = steps;
+    o.n_fixings = 3;
+    long points = 0;
+    for (bool done = false; !done; ++points) {
+        heston_ctx *c = nullptr;
+        fake::pending.clear();
+        CHECK(heston_ctx_create(0, nullptr, 0, &c) == HESTON_OK);
+        fake::fail_at = fake::calls + points;
+        heston_result r;
+        done = heston_price_greeks_ex(c, &P, HESTON_ASIAN_CALL, 10000, 12, 1, &o, &r) == HESTON_OK;
+        fake::fail_at = -1;
+        CHECK(!c->side || fake::pending[c->side] == 0);
+        CHECK(heston_ctx_destroy(c) == HESTON_OK);
+    }
+    CHECK(points > 20);
+}
+
 int main()
 {
+    control_error_returns();
     exact_budget();
     control_budget();
     for (auto &f : fake::faults) {
