@@ -21,6 +21,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ("api.hip", "price_kernel.hip", "adjoint_kernel.hip", "batch_kernel.hip",
            "batch_api.hip", "server.hip", "geo_control.hip", "exact_kernel.hip")
 SRC = [os.path.join(HERE, "csrc", f) for f in SOURCES]
+# compiled a second time for launches of few waves (csrc/device_math.hpp)
+FEW_WAVES = ("price_kernel.hip", "adjoint_kernel.hip", "batch_kernel.hip")
 HDRS = [os.path.join(HERE, "csrc", f) for f in ("internal.hpp", "device_math.hpp", "fp64_math.hpp",
                                                 "fp64_tables.hpp",
                                                 "inv_normal_coef.hpp", "cplx.hpp",
@@ -44,10 +46,11 @@ PER_FILE = {
 }
 
 
-def _compile(hipcc: str, src: str, verbose: bool) -> str:
+def _compile(hipcc: str, src: str, few_waves: bool, verbose: bool) -> str:
     name = os.path.basename(src)
-    obj = os.path.join(OBJ_DIR, name + ".o")
-    cmd = [hipcc, *FLAGS, *PER_FILE.get(name, []), "-c", "-o", obj + ".tmp", src]
+    obj = os.path.join(OBJ_DIR, name + (".few_waves.o" if few_waves else ".o"))
+    cmd = [hipcc, *FLAGS, *PER_FILE.get(name, []), *(["-DHESTON_FEW_WAVES"] if few_waves else []),
+           "-c", "-o", obj + ".tmp", src]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
@@ -58,9 +61,10 @@ def _compile(hipcc: str, src: str, verbose: bool) -> str:
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
-    workers = max(1, min(len(SRC), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
+    jobs = [(s, False) for s in SRC] + [(s, True) for s in SRC if os.path.basename(s) in FEW_WAVES]
+    workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
     with ThreadPoolExecutor(workers) as ex:
-        objs = list(ex.map(lambda s: _compile(hipcc, s, verbose), SRC))
+        objs = list(ex.map(lambda j: _compile(hipcc, *j, verbose), jobs))
     tmp = LIB + ".tmp"
     cmd = [hipcc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs]
     if verbose:

@@ -13,6 +13,7 @@
 // The payoff seeds follow the pathwise estimators of the paper's section
 // "Pathwise method for greeks estimation" (chain rule through S_T or the
 // discrete average); dS0 and dr reproduce the pathwise Delta and Rho.
+#define HESTON_OPAQUE_TRANS // see device_math.hpp
 #include "device_math.hpp"
 #include "internal.hpp"
 #include "path_step.hpp"
@@ -167,16 +168,34 @@ hipError_t launch_fwd_r(const PriceLaunch &L, hipStream_t s)
 
 } // namespace
 
+#ifdef HESTON_FEW_WAVES
+hipError_t launch_adjoint_forward_few_waves(const PriceLaunch &L, hipStream_t stream)
+{
+    return launch_fwd_r<float>(L, stream);
+}
+
+hipError_t launch_adjoint_few_waves(const PriceLaunch &L, double seed_grad, double *per_path,
+                                    hipStream_t stream)
+{
+    return launch_r<float>(L, seed_grad, per_path, stream);
+}
+#else
+static bool few_waves(const PriceLaunch &L) { return few_waves((L.n_paths + BLOCK - 1) / BLOCK, false); }
+
 hipError_t launch_adjoint_forward(const PriceLaunch &L, hipStream_t stream)
 {
-    return L.precision == 0 ? launch_fwd_r<double>(L, stream) : launch_fwd_r<float>(L, stream);
+    return L.precision == 0 ? launch_fwd_r<double>(L, stream)
+           : few_waves(L)   ? launch_adjoint_forward_few_waves(L, stream)
+                            : launch_fwd_r<float>(L, stream);
 }
 
 hipError_t launch_adjoint(const PriceLaunch &L, double seed_grad, double *per_path,
                           hipStream_t stream)
 {
     return L.precision == 0 ? launch_r<double>(L, seed_grad, per_path, stream)
+           : few_waves(L)   ? launch_adjoint_few_waves(L, seed_grad, per_path, stream)
                             : launch_r<float>(L, seed_grad, per_path, stream);
 }
+#endif
 
 } // namespace heston

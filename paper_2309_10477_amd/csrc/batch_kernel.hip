@@ -17,6 +17,7 @@
 // Work) in R, payoff and pathwise estimators in FP64; in adjoint mode the
 // path's forward pass also stores checkpoints in the workgroup's scratch slot
 // and the reverse sweep follows immediately.
+#define HESTON_OPAQUE_TRANS // see device_math.hpp
 #include "device_math.hpp"
 #include "internal.hpp"
 #include "path_step.hpp"
@@ -125,6 +126,7 @@ void batch_kernel(const BatchOption *__restrict__ opts,
     }
 }
 
+#ifndef HESTON_FEW_WAVES
 // Option o's sums: its unit records added in unit order.  Thread t owns
 // column t % N_ACC and units u = t / N_ACC (mod BLOCK / N_ACC); the
 // BLOCK / N_ACC per-column partials are then added in a fixed order.
@@ -160,15 +162,6 @@ template <class R, int SC, bool ADJ> int resident_blocks()
     return cus * (per_cu > 0 ? per_cu : 1);
 }
 
-template <class R, int SC, bool ADJ>
-hipError_t launch_t(const BatchLaunch &B, hipStream_t s)
-{
-    hipLaunchKernelGGL((batch_kernel<R, SC, ADJ>), dim3(B.grid), dim3(BLOCK), 0, s, B.opts,
-                       B.item_opt, B.item_begin, B.item_end, B.counter, B.scratch,
-                       B.scratch_per_block);
-    return hipGetLastError();
-}
-
 template <class R, int SC> int resident_sc(bool adj)
 {
     return adj ? resident_blocks<R, SC, true>() : resident_blocks<R, SC, false>();
@@ -178,6 +171,16 @@ template <class R> int resident_r(int scheme, bool adj)
 {
     return scheme == 0 ? resident_sc<R, 0>(adj) : scheme == 1 ? resident_sc<R, 1>(adj)
                                                               : resident_sc<R, 2>(adj);
+}
+#endif
+
+template <class R, int SC, bool ADJ>
+hipError_t launch_t(const BatchLaunch &B, hipStream_t s)
+{
+    hipLaunchKernelGGL((batch_kernel<R, SC, ADJ>), dim3(B.grid), dim3(BLOCK), 0, s, B.opts,
+                       B.item_opt, B.item_begin, B.item_end, B.counter, B.scratch,
+                       B.scratch_per_block);
+    return hipGetLastError();
 }
 
 template <class R, int SC> hipError_t launch_sc(const BatchLaunch &B, hipStream_t s)
@@ -193,6 +196,9 @@ template <class R> hipError_t launch_r(const BatchLaunch &B, hipStream_t s)
 
 } // namespace
 
+#ifdef HESTON_FEW_WAVES
+hipError_t launch_batch_few_waves(const BatchLaunch &B, hipStream_t s) { return launch_r<float>(B, s); }
+#else
 // scheme: HESTON_FULL_TRUNCATION (0), HESTON_ABSORPTION (1) or HESTON_QE (2).
 int batch_resident_blocks(int precision, int scheme, bool adjoint)
 {
@@ -201,7 +207,9 @@ int batch_resident_blocks(int precision, int scheme, bool adjoint)
 
 hipError_t launch_batch(const BatchLaunch &B, hipStream_t s)
 {
-    return B.precision == 0 ? launch_r<double>(B, s) : launch_r<float>(B, s);
+    return B.precision == 0            ? launch_r<double>(B, s)
+           : few_waves(B.grid, false) ? launch_batch_few_waves(B, s)
+                                      : launch_r<float>(B, s);
 }
 
 hipError_t launch_batch_reduce(const BatchLaunch &B, double *sums, hipStream_t s)
@@ -209,5 +217,6 @@ hipError_t launch_batch_reduce(const BatchLaunch &B, double *sums, hipStream_t s
     hipLaunchKernelGGL(batch_reduce_kernel, dim3(B.n_opts), dim3(BLOCK), 0, s, B.opts, sums);
     return hipGetLastError();
 }
+#endif
 
 } // namespace heston

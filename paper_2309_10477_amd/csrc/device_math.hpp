@@ -23,22 +23,45 @@ namespace heston {
 // 611 -> 544 us, QE 1342 -> 1133; adjoint Asian 2^21 x 365 2222 -> 2000; a batch of
 // 64 options 5440 -> 4760.
 // The s_setprio behind the instruction is also the one wait state that a
-// transcendental's result needs before a plain instruction reads it.
-#define HESTON_TRANS_F32(name, op, src)                                                            \
+// transcendental's result needs before a plain instruction reads it.  (The
+// compiler's hazard pass does not see the definition inside the asm: a reader that
+// needs more wait states, such as a DPP move or a lane read, must not take these
+// results directly.)
+// A wave alone on its SIMD gains nothing and issues the two s_setprio as well (10 000
+// paths x 100: European 43.2 -> 47.3 us), so the kernels' files are compiled a second
+// time with HESTON_FEW_WAVES, the same instructions without them, for launches that
+// few_waves (internal.hpp) names.  With HESTON_OPAQUE_TRANS (adjoint and batch) the
+// results stay opaque to the compiler there as well: it keeps the QE branches apart
+// (adjoint QE Asian, reverse 74 instead of 87 us), while the price kernels schedule
+// better without.
+#ifndef HESTON_FEW_WAVES
+#define HESTON_TRANS_F32(name, op, src, plain)                                                     \
     __device__ __forceinline__ float name(float x)                                                 \
     {                                                                                              \
         float r;                                                                                   \
         asm("s_setprio 1\n\t" op " %0, " src "%1\n\ts_setprio 0" : "=v"(r) : "v"(x));            \
         return r;                                                                                  \
     }
-HESTON_TRANS_F32(sqrt_f32, "v_sqrt_f32", "")
-HESTON_TRANS_F32(sqrt_neg_f32, "v_sqrt_f32", "-") // sqrt(-x)
-HESTON_TRANS_F32(rsq_f32, "v_rsq_f32", "")
-HESTON_TRANS_F32(rcp_f32, "v_rcp_f32", "")
-HESTON_TRANS_F32(log2_f32, "v_log_f32", "")
-HESTON_TRANS_F32(exp2_f32, "v_exp_f32", "")
-HESTON_TRANS_F32(cos_rev_f32, "v_cos_f32", "") // argument in revolutions
-HESTON_TRANS_F32(sin_rev_f32, "v_sin_f32", "")
+#elif defined(HESTON_OPAQUE_TRANS)
+#define HESTON_TRANS_F32(name, op, src, plain)                                                     \
+    __device__ __forceinline__ float name(float x)                                                 \
+    {                                                                                              \
+        float r = plain;                                                                           \
+        asm("" : "+v"(r));                                                                         \
+        return r;                                                                                  \
+    }
+#else
+#define HESTON_TRANS_F32(name, op, src, plain)                                                     \
+    __device__ __forceinline__ float name(float x) { return plain; }
+#endif
+HESTON_TRANS_F32(sqrt_f32, "v_sqrt_f32", "", __builtin_amdgcn_sqrtf(x))
+HESTON_TRANS_F32(sqrt_neg_f32, "v_sqrt_f32", "-", __builtin_amdgcn_sqrtf(-x)) // sqrt(-x)
+HESTON_TRANS_F32(rsq_f32, "v_rsq_f32", "", __builtin_amdgcn_rsqf(x))
+HESTON_TRANS_F32(rcp_f32, "v_rcp_f32", "", __builtin_amdgcn_rcpf(x))
+HESTON_TRANS_F32(log2_f32, "v_log_f32", "", __builtin_amdgcn_logf(x))
+HESTON_TRANS_F32(exp2_f32, "v_exp_f32", "", __builtin_amdgcn_exp2f(x))
+HESTON_TRANS_F32(cos_rev_f32, "v_cos_f32", "", __builtin_amdgcn_cosf(x)) // argument in revolutions
+HESTON_TRANS_F32(sin_rev_f32, "v_sin_f32", "", __builtin_amdgcn_sinf(x))
 #undef HESTON_TRANS_F32
 
 // ---------------------------------------------------------------------------

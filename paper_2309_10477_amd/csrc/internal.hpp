@@ -29,6 +29,19 @@ constexpr int N_ACC_CV = 2 * N_EST_CV;
 constexpr int DUMP_WIDTH = 16;
 constexpr int BLOCK = 256;         // threads per block of the path kernels
 constexpr int MAX_BRIDGE_DEPTH = 24;
+// Single-precision launches that leave a SIMD at most one wave (a block of four
+// waves per CU) run the kernels without raised priorities (device_math.hpp).  Calls
+// of up to 65536 paths x 100 steps take 44 instead of 48 us (European with bumps), 52
+// instead of 61 (every-step Asian), the adjoint's European reverse sweep 24 instead
+// of 27; from 98304 paths on the raised priorities are level or faster (European
+// 58 / 55 us, at 393216 paths 111 / 97).  The Sobol walk, with more plain
+// instructions to a transcendental, gains from them later: 131072 paths x 64 steps
+// 77 / 81 us, 163840 equal.
+constexpr uint64_t FEW_WAVES_BLOCKS = 256, FEW_WAVES_BLOCKS_SOBOL = 512;
+inline bool few_waves(uint64_t blocks, bool sobol)
+{
+    return blocks <= (sobol ? FEW_WAVES_BLOCKS_SOBOL : FEW_WAVES_BLOCKS);
+}
 // Fourth Philox counter word of the QE scheme's per-step block.
 constexpr uint32_t QE_COUNTER_TAG = 4u;
 // Scenario-split layout of small FP64 bump launches (price_kernel SPLIT): paths
@@ -211,6 +224,7 @@ struct BatchLaunch {
 };
 int batch_resident_blocks(int precision, int scheme, bool adjoint);
 hipError_t launch_batch(const BatchLaunch &B, hipStream_t s);
+hipError_t launch_batch_few_waves(const BatchLaunch &B, hipStream_t s); // launch_batch's, FP32
 // sums[o][N_ACC]: option o's unit records (at opts[o].partials) added in order.
 hipError_t launch_batch_reduce(const BatchLaunch &B, double *sums, hipStream_t s);
 
@@ -231,6 +245,7 @@ inline uint64_t ckpt_bytes(uint64_t n_paths, uint32_t n_steps, uint32_t every, s
 // L.ckpt every L.ckpt_every steps; block partials of (price, pathwise Delta,
 // pathwise Rho) in L.partials as for launch_paths.
 hipError_t launch_adjoint_forward(const PriceLaunch &L, hipStream_t stream);
+hipError_t launch_adjoint_forward_few_waves(const PriceLaunch &L, hipStream_t stream); // its, FP32
 
 // Adjoint sums: price and the derivatives of the discounted payoff with respect
 // to (S0, v0, r, kappa, theta, sigma, rho), each as (sum, sum of squares).
@@ -242,6 +257,8 @@ enum AdjointOut : int { ADJ_PRICE = 0, ADJ_S0, ADJ_V0, ADJ_R, ADJ_KAPPA, ADJ_THE
 // (payoff and the seven derivatives) scaled by `seed_grad`.
 hipError_t launch_adjoint(const PriceLaunch &L, double seed_grad, double *per_path,
                           hipStream_t stream);
+hipError_t launch_adjoint_few_waves(const PriceLaunch &L, double seed_grad, double *per_path,
+                                    hipStream_t stream); // launch_adjoint's, FP32
 
 // Plain bump-and-revalue: per-path central differences of n_bump pairs of
 // payoff rows.  pay = [1 + 2 n_bump][n_paths] (row 0 the base scenario, rows
@@ -263,6 +280,7 @@ hipError_t launch_reduce_rows(const double *partials, uint32_t rows, uint32_t w,
 
 // Launches the path kernel of `L` on `stream` (one partial record per block).
 hipError_t launch_paths(const PriceLaunch &L, hipStream_t stream);
+hipError_t launch_paths_few_waves(const PriceLaunch &L, hipStream_t stream); // launch_paths's, FP32
 // Sums the partial records of each replicate, in a fixed order, into
 // `rep_sums` (device [n_reps][L.acc_width()]).
 hipError_t launch_reduce(const PriceLaunch &L, double *rep_sums, hipStream_t stream);

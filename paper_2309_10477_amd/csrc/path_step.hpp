@@ -301,7 +301,8 @@ __device__ __forceinline__ void adjoint_path(const PathConsts &k, uint64_t p, co
                 // s = sqrt(V+ dt) and NS ds/dV+ = NS dt / (2 s) from one reciprocal
                 // square root
                 const R s2 = vp * (CS * c.dt);
-                const R rs = pos ? fast_rsqrt(s2) : R(0);
+                const R rs0 = fast_rsqrt(s2); // ahead of the select: no branch around its asm
+                const R rs = pos ? rs0 : R(0);
                 const R s = s2 * rs;
                 const R dsdv = half_dt_ns * rs;
                 const R g = xbar * (za * dsdv - c.half_dt) + vbar * (ns.sigma * z2 * dsdv - c.kdt);

@@ -116,9 +116,9 @@ template <class R> __device__ __forceinline__ Grid<R> grid(const StepCoef &c, do
 
 // max(w, 0) as one v_med3 (no NaN canonicalisation of the loop-carried w).
 __device__ __forceinline__ float clamp0(float w) { return __builtin_amdgcn_fmed3f(w, 0.0f, 3.0e38f); }
-__device__ __forceinline__ double clamp0(double w) { return w > 0.0 ? w : 0.0; }
+[[maybe_unused]] __device__ __forceinline__ double clamp0(double w) { return w > 0.0 ? w : 0.0; }
 __device__ __forceinline__ float exp2r(float y) { return exp2_f32(y); }
-__device__ __forceinline__ double exp2r(double y) { return exp2_plain(y); }
+[[maybe_unused]] __device__ __forceinline__ double exp2r(double y) { return exp2_plain(y); }
 
 // One scaled step on grid g; z1l = Z1 / ln 2, a_g = kappa theta dt^2 +
 // sigma^2 dt^2 (Z2^2 - 1) / 4, s_g = sigma dt Z2.  y leaves out the
@@ -204,9 +204,9 @@ template <class R> __device__ __forceinline__ QEGrid<R> qe_grid(const StepCoef &
 }
 
 __device__ __forceinline__ float fast_log(float x) { return log2_f32(x) * (float)LN2; }
-__device__ __forceinline__ double fast_log(double x) { return log(x); }
+[[maybe_unused]] __device__ __forceinline__ double fast_log(double x) { return log(x); }
 __device__ __forceinline__ float fast_rcp(float x) { return rcp_f32(x); }
-__device__ __forceinline__ double fast_rcp(double x) { return rcp_pos(x); }
+[[maybe_unused]] __device__ __forceinline__ double fast_rcp(double x) { return rcp_pos(x); }
 
 // The variance step of one scenario, in parts; zv the normal of the quadratic
 // branch, uv the uniform of the exponential one.  psi = 2 h / m^2 <= 3/2 takes
@@ -876,6 +876,7 @@ __attribute__((amdgpu_waves_per_eu(SCH == 2 && sizeof(R) == 4 ? 4 : 1))) void pr
 // group sums of each column, are added in order.  One workgroup reads at a
 // few tens of GB/s, so long replicates are first cut into chunks of
 // REDUCE_CHUNK records, one block each, and the chunk sums reduced again.
+#ifndef HESTON_FEW_WAVES // (the rest has no path loop)
 constexpr int RB = 1024; // threads of a reduction block
 template <int W>
 __global__ __launch_bounds__(RB) void reduce_partials(const double *__restrict__ in,
@@ -1081,6 +1082,7 @@ __global__ void sobol_shift_kernel(uint64_t seed, const int32_t *perm, uint32_t 
     const U4 w = philox4x32_10(U4{d, r, 0u, 1u}, (uint32_t)seed, (uint32_t)(seed >> 32));
     out[idx] = w.x >> 2;
 }
+#endif
 
 template <class R, int RNG, int AV, bool BUMPS, int SCH>
 hipError_t launch_t(const PriceLaunch &L, hipStream_t s)
@@ -1137,6 +1139,12 @@ template <class R> hipError_t launch_r(const PriceLaunch &L, hipStream_t s)
 
 } // namespace
 
+#ifdef HESTON_FEW_WAVES
+hipError_t launch_paths_few_waves(const PriceLaunch &L, hipStream_t stream)
+{
+    return launch_r<float>(L, stream);
+}
+#else
 hipError_t launch_step_weights(const PriceLaunch &L, void *out, hipStream_t stream)
 {
     const uint32_t n = L.n_steps;
@@ -1177,7 +1185,10 @@ hipError_t launch_sobol_shifts(uint64_t seed, const int32_t *perm, uint32_t dims
 
 hipError_t launch_paths(const PriceLaunch &L, hipStream_t stream)
 {
-    return L.precision == 0 ? launch_r<double>(L, stream) : launch_r<float>(L, stream);
+    return L.precision == 0 ? launch_r<double>(L, stream)
+           : few_waves((uint64_t)L.blocks_per_rep * L.n_reps, L.rng == 1)
+               ? launch_paths_few_waves(L, stream)
+               : launch_r<float>(L, stream);
 }
 
 hipError_t launch_bump_combine(const double *pay, uint64_t n_paths, uint32_t n_bump,
@@ -1202,5 +1213,6 @@ hipError_t launch_reduce(const PriceLaunch &L, double *rep_sums, hipStream_t str
     return L.cv ? launch_reduce_w<N_ACC_CV>(L, rep_sums, stream)
                 : launch_reduce_w<N_ACC>(L, rep_sums, stream);
 }
+#endif
 
 } // namespace heston

@@ -188,6 +188,20 @@ def test_adjoint_qe_against_analytic(hm, ctx):
         assert abs(g2[k][0] - ref[k]) < allow, (k, g2[k], g1[k], ref[k])
 
 
+@pytest.mark.parametrize("opt_type,scheme", [(0, 0), (2, 1), (2, 2)])
+def test_fp32_adjoint_is_the_same_in_small_and_large_launches(hm, ctx, opt_type, scheme):
+    """At most one wave per SIMD (65536 paths) and one block more: other builds
+    of the kernels, the same derivatives of each path, bit for bit; and the same
+    option alone in a batch and beside a large one."""
+    d = [adjoint_per_path(hm, ctx, PB, opt_type, n, 9, 5, 1, 8, scheme)[2] for n in (65536, 65792)]
+    assert np.array_equal(d[0], d[1][:65536])
+    opts = hm.Options(precision=hm.FP32, scheme=scheme, greeks=hm.GREEKS_PATHWISE)
+    rq = [dict(params=PB.__dict__, type=opt_type, n_steps=9, n_paths=n, seed=5, want=hm.WANT_ADJOINT)
+          for n in (8192, 1 << 18)]
+    alone, beside = (ctx.price_batch(r, opts)[0][0] for r in (rq[:1], rq))
+    assert alone["price"] == beside["price"] and alone["adj"] == beside["adj"]
+
+
 def test_adjoint_seed_gradient_scales(hm, ctx):
     n, N = 1000, 20
     _, g1, d1 = adjoint_per_path(hm, ctx, PB, 0, n, N, 3, 0, 8)

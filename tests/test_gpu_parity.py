@@ -224,6 +224,21 @@ def test_fp32_every_step_fixing(hm, ctx, opt_type, N, scheme):
     check_records(d, PB, opt_type, N, 7, 0, 500, 1, scheme, None, True)
 
 
+@pytest.mark.parametrize("opt_type,scheme,rng", [
+    (oracle.EURO_CALL, 0, 0), (oracle.ASIAN_PUT, 1, 0), (oracle.GEO_ASIAN_CALL, 2, 0),
+    (oracle.ASIAN_CALL, 2, 0), (oracle.EURO_PUT, 6, 0), (oracle.ASIAN_CALL, 0, 1)])
+def test_fp32_paths_are_the_same_in_small_and_large_launches(hm, ctx, opt_type, scheme, rng):
+    """A launch of at most one wave per SIMD (two under Sobol) runs kernels built
+    without raised priorities: the same first paths, bit for bit, from the
+    largest such launch and from one block more."""
+    limit = 65536 if rng == 0 else 131072
+    N, seed, n = 9, 5, limit + 256
+    opts = hm.Options(precision=hm.FP32, scheme=scheme, rng=rng, qmc_replicates=1)
+    small = dump(hm, ctx, PB, opt_type, n, N, seed, 0, limit, opts)
+    large = dump(hm, ctx, PB, opt_type, n, N, seed, 0, n, opts)
+    assert np.array_equal(small, large[:limit], equal_nan=True)
+
+
 @pytest.mark.parametrize("scheme", [3, 4, 5, 6])
 def test_euler_and_fixes_fp32(hm, ctx, scheme):
     n, N, seed = 4096 + 100, 63, 9
