@@ -8,9 +8,13 @@
 // With these forms a step of the fused arithmetic-Asian kernel issues 237
 // instead of 430 VALU instructions and one of the scenario-split European
 // kernel 40 instead of 65: a daily Asian put with fused bumps, 200 003 paths x
-// 251 steps, 882 -> 495 us per call; a 64-option FP64 batch 1.95x.  The
-// averages' errors against an 80-bit simulation are unchanged (rms 4.4e-16
-// relative after 252 steps, before and after).
+// 251 steps, 882 -> 495 us per call; a 64-option FP64 batch 1.95x.
+// Each function's error in ulps is checked on the CPU (tests/host/fp64_math_test.cpp):
+// the Box-Muller radius 0.37 rms (the library's 0.33), cosine and sine 0.34 of
+// 2^-53, exponentials 0.30 (at most 0.89), square root and reciprocal correctly
+// rounded.  The averages of 252-step paths, measured against an 80-bit simulation,
+// were off by 4.4e-16 rms before and after (base parameters); by 6.4e-15 before and
+// 7.6e-15 after, with the same median, on a long Feller-violating set.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,8 +51,8 @@ template <int BLOCK_SIZE> __device__ __forceinline__ void load_fp64_tables()
 
 // -2 ln(d 2^-shift) of a normal d > 0: d = z 2^k with z in [0.70801, 1.41602),
 // and the value is (shift - k) 2 ln 2 - 2 ln c - 2 ln(1 + r), r = z / c - 1,
-// |r| < 2^-9, the last by its series through r^6 (truncation below 2^-65
-// relative to r).
+// |r| < 2^-9, the last by its series through r^6 (truncation below 2^-64.8, or
+// 2^-55.8 relative to r).
 __device__ __forceinline__ double neg2_log(double d, int shift)
 {
     const int t = __double2hiint(d) - (int)LOG_OFFSET;
@@ -71,7 +75,7 @@ __device__ __forceinline__ double neg2_log_uniform(uint32_t w)
 }
 
 // (C + i S) e^{i d} for a table angle (C, S) and |d| <= pi / 256: the addition
-// theorems with the series of sin d and cos d - 1 (truncations below 2^-68).
+// theorems with the series of sin d and cos d - 1 (truncations below 2^-75 and 2^-66).
 __device__ __forceinline__ void turn(double C, double S, double d, double &c, double &s)
 {
     const double q = d * d;
@@ -133,7 +137,7 @@ __device__ __forceinline__ double rsqrt_pos(double x)
 }
 
 // 2^y: y = n + f, |f| <= 1/2, and 2^f = 1 + f q(f), q of degree 10 (near-minimax
-// over [-1/2, 1/2], 1.3e-17); v_ldexp saturates to 0 and infinity by itself.
+// over [-1/2, 1/2], 2.0e-17); v_ldexp saturates to 0 and infinity by itself.
 __device__ __forceinline__ double exp2_plain(double y)
 {
     const double n = rint(y), f = y - n;
@@ -152,7 +156,7 @@ __device__ __forceinline__ double exp2_plain(double y)
 }
 
 // e^x: x = n ln 2 + f with ln 2 in two parts, e^f = 1 + f q(f), q of degree 10
-// (near-minimax over |f| <= ln 2 / 2, 1.8e-17).  For |x| up to 1e40: f is of the
+// (near-minimax over |f| <= ln 2 / 2, 9.8e-18).  For |x| up to 1e40: f is of the
 // order of x's last place there, and its eleventh power overflows beyond.
 __device__ __forceinline__ double exp_plain(double x)
 {
@@ -183,7 +187,7 @@ __device__ __forceinline__ double log_pos(double x) { return -0.5 * neg2_log(x, 
 // The argument of x + i y, (x, y) away from 0 and the ends of single precision's
 // range: a single-precision estimate (7e-4) picks the nearest table angle n pi / 128;
 // the rest is atan of the turned vector's slope, |slope| < 0.0133, by its
-// series (truncation below 2^-60).
+// series (truncation below 2^-59).
 __device__ __forceinline__ double angle(double x, double y)
 {
     const float xf = (float)x, yf = (float)y, ax = fabsf(xf), ay = fabsf(yf);

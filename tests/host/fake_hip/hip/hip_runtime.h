@@ -4,6 +4,7 @@
 // may be made to: the one numbered fake::fail_at.
 #pragma once
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <cstdlib>
@@ -16,6 +17,47 @@
 #define __host__
 #define __align__(n) __attribute__((aligned(n)))
 #define __forceinline__ inline
+#define __shared__ static
+
+// Device intrinsics of the elementary functions: a block of one thread, and the
+// hardware's estimates of 1 / x and 1 / sqrt(x) off by fake::estimate_error.
+namespace fake {
+inline double estimate_error = 0;
+inline double bits(uint64_t b)
+{
+    double x;
+    memcpy(&x, &b, 8);
+    return x;
+}
+inline uint64_t bits(double x)
+{
+    uint64_t b;
+    memcpy(&b, &x, 8);
+    return b;
+}
+} // namespace fake
+struct FakeDim {
+    unsigned x, y, z;
+};
+static const FakeDim threadIdx = {0, 0, 0};
+inline void __syncthreads() {}
+inline int __double2hiint(double x) { return (int)(fake::bits(x) >> 32); }
+inline int __double2loint(double x) { return (int)(uint32_t)fake::bits(x); }
+inline double __hiloint2double(int hi, int lo)
+{
+    return fake::bits((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+inline double fake_rcp(double x) { return (double)(1.0L / x * (1.0L + fake::estimate_error)); }
+inline double fake_rsq(double x) { return (double)(1.0L / sqrtl(x) * (1.0L + fake::estimate_error)); }
+// v_cvt_i32_f64 saturates and takes NaN to 0
+inline double fake_ldexp(double x, double n)
+{
+    return n != n ? x : ldexp(x, (int)fmin(fmax(n, -2147483648.0), 2147483647.0));
+}
+#define __builtin_amdgcn_rcp fake_rcp
+#define __builtin_amdgcn_rsq fake_rsq
+#define __builtin_amdgcn_rcpf(x) (1.0f / (x))
+#define __builtin_amdgcn_ldexp(x, n) fake_ldexp(x, (double)(n))
 
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorUnknown = 999 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 };
