@@ -336,8 +336,9 @@ void plan_launch(const Request &q, uint64_t first, uint64_t count, PriceLaunch &
 }
 
 // Few FP64 paths with fused bumps (Philox, Milstein or Euler, European or
-// arithmetic Asian, no control) take one scenario per lane: at most about one
-// wave per SIMD, and a wave's work per step roughly halves (price_kernel SPLIT).
+// arithmetic Asian, no control) take one scenario per lane: up to three or four
+// such waves per SIMD (12288 paths each), a wave's work per step being much less
+// than a fused one's (price_kernel SPLIT).
 bool split_layout(const Request &q, const PriceLaunch &L, uint64_t count)
 {
     return q.o.precision == HESTON_FP64 && L.rng == HESTON_RNG_PHILOX && L.bumps && !L.cv &&
@@ -1011,7 +1012,6 @@ static heston_status run_exact(heston_ctx *c, const Request &q, uint64_t first, 
     E.nu = 2.0 * p.kappa * p.theta / s2 - 1.0;
     E.kappa2 = p.kappa * p.kappa;
     E.two_sigma2 = 2.0 * s2;
-    E.sigma2 = s2;
     E.inv_sigma2 = 1.0 / s2;
     E.t1_const = std::log(1.0 - ek) - std::log(p.kappa) + 0.5 * p.kappa * E.D;
     E.coth_k = p.kappa * (1.0 + ek) / (1.0 - ek);

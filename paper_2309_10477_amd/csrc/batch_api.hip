@@ -53,7 +53,7 @@ BatchOption batch_option(const heston_request &r)
     k.sigma = p.sigma;
     k.theta = p.theta;
     k.seed = r.seed;
-    k.fix_bits = nullptr;
+    k.fix_bits = nullptr; // the batch kernel's Milstein forward pass sums every step
     k.n_steps = r.n_steps;
     k.n_fix = r.type >= 2 ? r.n_steps : 1;
     k.type = r.type;

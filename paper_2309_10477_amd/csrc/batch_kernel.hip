@@ -44,7 +44,8 @@ __device__ __forceinline__ void run_unit_paths(const BatchOption &op, uint64_t c
             __threadfence_block();
             adjoint_path_qe<R, ASIAN, BATCH_CKPT_EVERY>(op.k, p, scratch, BLOCK, tid, out);
         } else {
-            // (batched Asians fix at every step)
+            // (batched Asians fix at every step: batch_option leaves fix_bits null, and
+            // the callers refuse fixing dates)
             forward_steps<R, ASIAN, SC == 0, true>(op.k, p, x, v, A, B, scratch, BLOCK, tid,
                                                    BATCH_CKPT_EVERY);
             __threadfence_block();

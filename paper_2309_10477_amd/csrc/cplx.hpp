@@ -1,6 +1,6 @@
 // Double-precision complex arithmetic for device code (the semi-analytic
 // geometric price and the exact sampler's characteristic function): plain
-// struct, principal branches throughout.
+// struct.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -34,19 +34,6 @@ __device__ __forceinline__ Cx cexp(Cx z)
     sincos(z.im, &s, &c);
     const double e = exp(z.re);
     return {e * c, e * s};
-}
-// Principal branch.
-__device__ __forceinline__ Cx clog(Cx z) { return {log(hypot(z.re, z.im)), atan2(z.im, z.re)}; }
-// Principal square root (non-negative real part).
-__device__ __forceinline__ Cx csqrt(Cx z)
-{
-    const double m = hypot(z.re, z.im);
-    if (m == 0.0)
-        return {0.0, 0.0};
-    const double t = sqrt(0.5 * (m + fabs(z.re)));
-    if (z.re >= 0.0)
-        return {t, z.im / (2.0 * t)};
-    return {fabs(z.im) / (2.0 * t), copysign(t, z.im)};
 }
 __device__ __forceinline__ Cx operator*(double s, Cx a) { return {a.re * s, a.im * s}; }
 __device__ __forceinline__ Cx operator-(Cx a) { return {-a.re, -a.im}; }

@@ -21,7 +21,7 @@ namespace heston {
 // plain instructions between find no partner.  Letting a wave that has reached
 // one issue it first brings the six to 19.8 cycles.  At 2^20 x 252: daily Asian
 // 611 -> 544 us, QE 1342 -> 1133; adjoint Asian 2^21 x 365 2222 -> 2000; a batch of
-// 64 options 5440 -> 4760.
+// 64 options 5540 -> 4765.
 // The s_setprio behind the instruction is also the one wait state that a
 // transcendental's result needs before a plain instruction reads it.  (The
 // compiler's hazard pass does not see the definition inside the asm: a reader that

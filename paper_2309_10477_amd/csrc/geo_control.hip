@@ -26,7 +26,7 @@
 // telescope).  One thread per transform doing all of it in order was a chain of
 // 252 steps of some 6000 cycles each, 585 us for a daily Asian on 9 blocks,
 // longer than the 2^18 paths beside it; the chain is now sixteen FMAs per step,
-// the kernel takes about 45 us beside them and the call 250 instead of 627 us.
+// the kernel takes about 50 us beside them and the call 226 instead of 627 us.
 // Against an 80-bit evaluation the price's error is 1e-15 to 1e-12 relative,
 // smaller than the serial form's on 25 of 35 parameter and date sets.
 // The first pass integrates over [0, g.v_max] (a range the host sizes from
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(BLOCK) void geo_bound_kernel(const GeoControl g, do
     if (is_bound)
         bound[t] = bound_part(g, lt, v, which);
     else if (t == 2 * GEO_BOUND_POINTS)
-        out[2] = exp(lt.re); // E[G]
+        out[0] = exp(lt.re); // E[G]
 }
 
 // Range of the integral: the first 2^k (k <= GEO_MAX_LOG2_RANGE) whose bound
@@ -221,8 +221,8 @@ __device__ uint32_t range_from(const double *bound, double EG, double K)
 // Gauss-Legendre nodes of the integral over [0, range], two transforms per
 // node, from block `block0` of the whole range on; a later launch (block0 > 0)
 // adds to the partials of the one before.  With a `fixed` range the three slots
-// after the nodes evaluate the modulus bound at v = fixed (out[4], out[5]) and
-// E[G] (out[2]); otherwise the range comes from the bound table of
+// after the nodes evaluate the modulus bound at v = fixed (out[1], out[2]) and
+// E[G] (out[0]); otherwise the range comes from the bound table of
 // geo_bound_kernel.
 template <uint32_t SLOTS>
 __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uint32_t fixed,
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uin
 {
     __shared__ GeoShared<SLOTS> sh;
     constexpr uint32_t LANES = GeoShared<SLOTS>::LANES;
-    const uint32_t range = fixed ? fixed : range_from(bound, out[2], g.K);
+    const uint32_t range = fixed ? fixed : range_from(bound, out[0], g.K);
     const uint32_t width = range < GEO_PANEL_WIDTH ? range : GEO_PANEL_WIDTH;
     const uint32_t panels = width ? range / width : 0u;
     const uint32_t first = (block0 + blockIdx.x) * SLOTS, t = first + threadIdx.x / LANES;
@@ -258,9 +258,9 @@ __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uin
     if (threadIdx.x % LANES == 0) {
         sh.red[threadIdx.x / LANES] = is_node ? weight * integrand_part(g, lt, v, which) : 0.0;
         if (fixed && is_bound)
-            out[4 + which] = bound_part(g, lt, v, which);
+            out[1 + which] = bound_part(g, lt, v, which);
         else if (fixed && t == n_nodes + 2)
-            out[2] = exp(lt.re); // E[G]
+            out[0] = exp(lt.re); // E[G]
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -274,8 +274,8 @@ __global__ __launch_bounds__(BLOCK) void geo_node_kernel(const GeoControl g, uin
 
 __global__ __launch_bounds__(BLOCK) void geo_finish_kernel(const GeoControl g, uint32_t fixed,
                                                            uint32_t n_blocks, const double *bound,
-                                                           const double *partials, double *out,
-                                                           double *prices)
+                                                           const double *partials,
+                                                           const double *out, double *prices)
 {
     __shared__ double red[BLOCK];
     double s = 0.0;
@@ -289,15 +289,14 @@ __global__ __launch_bounds__(BLOCK) void geo_finish_kernel(const GeoControl g, u
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const double EG = out[2], I = red[0];
+        const double EG = out[0], I = red[0];
         const double D = exp(-g.r * g.T);
-        const bool ok = fixed ? out[4] + out[5] <= GEO_TOL * (EG + g.K)
+        const bool ok = fixed ? out[1] + out[2] <= GEO_TOL * (EG + g.K)
                               : range_from(bound, EG, g.K) != 0u;
         const double call = D * (0.5 * (EG - g.K) + I / M_PI);
         const double nan = __builtin_nan("");
         prices[0] = ok ? call : nan;
         prices[1] = ok ? call - D * (EG - g.K) : nan;
-        out[3] = I;
     }
 }
 

@@ -155,7 +155,7 @@ struct ExactLaunch {
     double d;            // 4 kappa theta / sigma^2 (degrees of freedom)
     double c;            // sigma^2 (1 - e^{-kappa D}) / (4 kappa)
     double ekD;          // e^{-kappa D}
-    double kappa2, two_sigma2, sigma2, inv_sigma2;
+    double kappa2, two_sigma2, inv_sigma2;
     double t1_const;     // ln(1 - e^{-kappa D}) - ln kappa + kappa D / 2
     double coth_k;       // kappa (1 + e^{-kappa D}) / (1 - e^{-kappa D})
     double log_zk_scale; // ln(4 kappa e^{-kappa D/2} / (sigma^2 (1 - e^{-kappa D})))
@@ -287,15 +287,15 @@ hipError_t launch_reduce(const PriceLaunch &L, double *rep_sums, hipStream_t str
 
 // Geometric-average control, in one device buffer `buf` of GEO_BUF_DOUBLES:
 // [0, 2 GEO_BOUND_POINTS) the modulus bounds |M(1 + iv)| / v and K |M(iv)| / v
-// at v = 2^k (M the transform of ln G; search only), then at GEO_OUT the
-// discounted call and put prices of G, E[G], the Gil-Pelaez integral and the
-// two bounds at the end of the fixed range.  The prices are NaN when the
-// transform has not decayed by the end of the range (fixed: g.v_max, at most
-// GEO_MAX_FIXED_RANGE; search: 2^14).  `partials` (device [GEO_NODE_BLOCKS])
-// holds one double per block of the node kernel.
+// at v = 2^k (M the transform of ln G; search only), then at GEO_OUT E[G] and the
+// two bounds at the end of the fixed range.  The discounted call and put prices
+// of G go to `prices`; they are NaN when the transform has not decayed by the end
+// of the range (fixed: g.v_max, at most GEO_MAX_FIXED_RANGE; search: 2^14).
+// `partials` (device [GEO_NODE_BLOCKS]) holds one double per block of the node
+// kernel.
 constexpr int GEO_BOUND_POINTS = 15;
 constexpr int GEO_OUT = 2 * GEO_BOUND_POINTS;
-constexpr int GEO_BUF_DOUBLES = GEO_OUT + 6;
+constexpr int GEO_BUF_DOUBLES = GEO_OUT + 3;
 constexpr uint32_t GEO_MAX_FIXED_RANGE = 4096;
 // Most blocks of a launch of the node kernel: a partial each, 16 KiB of the
 // context's budget.

@@ -228,11 +228,6 @@ template <class R> __device__ __forceinline__ QEPre<R> qe_pre(R w, const QEGrid<
     const R mm = m * m;
     return QEPre<R>{m, mm, h, h <= R(0.75) * mm};
 }
-template <class R> __device__ __forceinline__ R add_rounded(R a, R b)
-{
-#pragma clang fp contract(off)
-    return a + b;
-}
 // ROUND_ZV: zv enters as a rounded value (five scenarios share it), not as the
 // product of a fused multiply-add.
 template <class R, bool ROUND_ZV> __device__ __forceinline__ R qe_quad(const QEPre<R> &q, R zv)
@@ -241,7 +236,7 @@ template <class R, bool ROUND_ZV> __device__ __forceinline__ R qe_quad(const QEP
     const R b2 = inv - R(1) + fast_sqrt(inv * (inv - R(1)));
     const R a = q.m * fast_rcp(R(1) + b2);
     const R b = fast_sqrt(b2);
-    const R bz = ROUND_ZV ? add_rounded(b, zv) : b + zv;
+    const R bz = ROUND_ZV ? qe_shift(b, zv) : b + zv;
     return a * bz * bz;
 }
 template <class R> __device__ __forceinline__ R qe_expo(const QEPre<R> &q, R uv)
