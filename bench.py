@@ -65,10 +65,10 @@ TRAFFIC_BYTES_PER_LAUNCH = 845_414
 # profiles/valu_utilisation_counters.md.  Set to None whenever the kernel
 # changes until the counters are taken again.
 VALU_COUNTERS = {
-    "simd_valu_busy": 0.932,        # (SQ_ACTIVE_INST_VALU - SQ_ACTIVE_INST_VALU2) / SIMD quad-cycles
+    "simd_valu_busy": 0.936,        # (SQ_ACTIVE_INST_VALU - SQ_ACTIVE_INST_VALU2) / SIMD quad-cycles
     "valu_lane_util": 0.9994,       # SQ_THREAD_CYCLES_VALU / (SQ_ACTIVE_INST_VALU x 64)
-    "valu_utilisation": 0.931,      # their product: the path kernel's share of VALU issue capacity
-    "valubusy_amd_formula": 1.341,  # VALUBusy as rocprof defines it (counts dual-issued quad-cycles twice)
+    "valu_utilisation": 0.936,      # their product: the path kernel's share of VALU issue capacity
+    "valubusy_amd_formula": 1.348,  # VALUBusy as rocprof defines it (counts dual-issued quad-cycles twice)
     "counted_flop_per_path_step": 112.9,  # 64 x (SQ_INSTS_VALU_FLOPS_FP32 + _TRANS + FP64 + _TRANS) / path-steps
 }
 

@@ -53,7 +53,7 @@ struct heston_ctx {
     DevBuf bridge_start, bridge_ops;
     DevBuf pay, bump_partials, bump_sums, step_w;
     DevBuf geo_buf, geo_partials, geo_steps; // geometric-average control
-    DevBuf exact_scratch;                    // exact sampler: Re Phi per lane
+    DevBuf exact_scratch;                    // exact sampler: Re Phi per group
     DevBuf reduce_tmp;                       // first-level sums of long reductions
     DevBuf batch_opts, batch_items, batch_partials, batch_sums, batch_counter, batch_scratch;
     double *host_sums = nullptr;     // pinned
